@@ -57,7 +57,7 @@ MFMA_INT8_PEAK_TOPS = 5000.0   # MI355X dense int8, tera-ops/s
 HBM_PEAK_GBPS = 8000.0
 PMC_FILE = os.path.join(ROOT, "profiles", "corr_pathfinder_n256_f64_t16384_pmc.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1503_06189_amd", "csrc", f)
-                  for f in ("xcorr_kernels.hpp", "plan.hpp", "xengine.hip")]
+                  for f in ("xcorr_kernels.hpp", "short_kernels.hpp", "plan.hpp", "xengine.hip")]
 
 
 def kernel_source_hash() -> str:

@@ -1,4 +1,4 @@
-"""MI355X-native X-engine correlator (4+4-bit complex, int8 MFMA).
+"""MI355X-native X-engine correlator (4+4-bit complex, MFMA).
 
 Submodules:
   xengine  -- ctypes binding of libxengine.so (the HIP path)

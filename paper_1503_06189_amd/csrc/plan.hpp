@@ -2,31 +2,23 @@
 //
 // The triangle of 32x32 input-block tiles (I <= J) of each channel is cut
 // into "super-blocks" of 8x8 tiles (256 x 256 inputs).  A workgroup of eight
-// waves (two per SIMD, 128 accumulator registers each) takes one tile group:
-//   * a diagonal super-block: a triangle of 36 tiles, 8 on the diagonal
-//     and 28 off it.  A diagonal tile costs half (one MFMA chain, 16
-//     accumulator registers).  Waves 0..3 take the 1 x 4 rectangles of
-//     tiles (w, 4..7); waves 4..7 take the halves of the triangles of
-//     blocks 0..3 and 4..7 (2 diagonal tiles and 3 off-diagonal ones each);
-//   * half of an off-diagonal super-block: 4 tile rows x 8 tile columns.
-//     Wave w takes row w % 4 and columns 4 (w / 4) .. + 3.
-// Every wave thus runs 16 MFMAs per staged step, and the two waves of a
-// SIMD (w and w + 4) together run 32.  Super-blocks at the edge of the
-// triangle are padded: input blocks past ceil(N/32) are staged as zeros and
-// their tiles are computed but never stored, so every wave has a fixed,
-// compile-time tile pattern.  With ns = ceil(blocks / 8) super-rows there
-// are ns diagonal groups and ns(ns-1)/2 off-diagonal super-blocks of two
-// halves each: ns^2 groups.  Each workgroup integrates its tiles over one
-// chunk of the frame's time samples; chunk 0 writes the output and a merge
-// kernel adds the other chunks.
+// waves, two per SIMD, takes one tile group:
+//   * a diagonal super-block: a triangle of 36 tiles over two 128-input
+//     groups of four blocks;
+//   * half of an off-diagonal super-block: 4 tile rows (a 128-input group) x
+//     8 tile columns (two groups).
+// How the waves share a group's tiles is the kernels' matter.  Super-blocks
+// at the edge of the triangle are padded: tiles past N are computed but never
+// stored, so every wave has a fixed, compile-time tile pattern.  With
+// ns = ceil(blocks / 8) super-rows there are ns diagonal groups and
+// ns(ns-1)/2 off-diagonal super-blocks of two halves each: ns^2 groups.  Each
+// workgroup integrates its tiles over one chunk of the frame's time samples;
+// chunk 0 writes the output and a merge kernel adds the other chunks.
 //
-// Second geometry ("halves", for N <= 128, at most 4 input blocks): the
-// padded super-block would compute 36 tiles for the 10 of the 4-block
-// triangle.  Instead the 8 staged slots hold blocks 0..3 at two consecutive
-// 32-sample steps (slots 4..7 one step later), so a loop step covers 64
-// samples: waves 4 and 5 integrate the triangle over the even steps, waves
-// 6 and 7 over the odd ones, and the rectangle waves only stage.  At the end
-// waves 6 and 7 hand their sums to 4 and 5 through LDS, which write them.
+// Second geometry ("halves", for N <= 128, one 128-input group): the padded
+// super-block would compute 36 tiles for the 10 of the group's triangle.
+// Instead waves integrate the whole triangle over their own part of the
+// samples, and the sums are added at the end.
 #pragma once
 
 #include <stdint.h>
@@ -40,46 +32,60 @@
 namespace xe {
 
 constexpr int kBlk = 32;          // inputs per tile edge (one 32x32 MFMA)
-constexpr int kStep = 32;         // samples staged per step
+constexpr int kStep = 32;         // unit of time chunks, in samples
+constexpr int kLoop = 64;         // samples per loop step of the kernels
 constexpr int kSuper = 8;         // tile blocks per super-block edge
+constexpr int kGroupInputs = 128; // inputs of four strided blocks
 constexpr int kMaxSlots = 12;     // input blocks staged per workgroup
-constexpr int kTilesPerWave = 5;  // (Re, Im) tiles a wave writes out, at most
-constexpr int kWaves = 8;
-constexpr int kThreads = 64 * kWaves;
-// |Q| of a diagonal tile grows by at most 248 per sample: a chunk of at
-// most 2^18 steps (8,388,608 samples) keeps it inside int32
+constexpr int kSuperWaves = 8, kSuperThreads = 64 * kSuperWaves;
+constexpr int kSmallWaves = 4, kSmallThreads = 64 * kSmallWaves;   // halves geometry
+// Workspace of one tile group and time chunk, in int32 values: at least the
+// chunk's copy of the group's share of the output.
+constexpr int64_t kGroupPartial = 81920;
+// Chunks of at most this many 32-sample steps run on the int8 kernel
+// (short_kernels.hpp), longer ones on the 6-bit kernels (xcorr_kernels.hpp),
+// which pay more per workgroup and less per sample.  Measured, accumulating
+// unchunked frames, int8 against 6-bit, us per call:
+//   128 inputs, 256 channels:  512 samples 15.9 | 26.1, 1536: 28.2 | 33.7,
+//                              2048: 34 | 36, 4096: 66 | 49
+//   256 inputs, 256 channels:  256 samples 26.2 | 31.1, 512: 32.3 | 35.5,
+//                              768: 38 | 40, 1024: 45 | 45, 2048: 78 | 61
+//   2048 inputs, 16 channels:  256 samples 86 | 97, 768: 134 | 138,
+//                              2048: 283 | 231
+// kShortSteps is also the most validity words that the int8 kernel keeps (one
+// per lane).
+constexpr int kShortSteps = 64;        // halves geometry
+constexpr int kShortSuperSteps = 24;   // super geometry
+XE_HD inline int use_short(int small, int steps) {
+    return steps <= (small ? kShortSteps : kShortSuperSteps);
+}
+// longest chunk: 2^18 steps (8,388,608 samples)
 constexpr int kMaxStepsPerChunk = 1 << 18;
-// Raw bytes are loaded this many steps ahead of their use; a chunk is run
-// in whole rings of kDepth steps (the last ring padded with zeros), so the
-// byte offsets of a chunk plus 4 * kDepth 32-sample steps must stay below
-// 2^31.
+// Chunk lengths are multiples of kDepth steps, and the byte offsets of a chunk
+// plus 4 * kDepth steps stay below 2^31.
 #ifndef XE_DEPTH
 #define XE_DEPTH 4
 #endif
 constexpr int kDepth = XE_DEPTH;
 
-// longest chunk (in steps) whose byte offsets, lookahead included (twice the
-// ring in 32-sample steps: a halves loop step covers two), stay below 2^31
-// for F channels of N inputs
+// longest chunk (in steps) whose byte offsets, with 4 * kDepth steps of slack,
+// stay below 2^31 for F channels of N inputs
 inline int64_t max_steps_per_chunk(int64_t F, int64_t N) {
     int64_t m = (((int64_t)1 << 31) - 1) / (F * N * kStep) - 4 * kDepth;
     if (m > kMaxStepsPerChunk) m = kMaxStepsPerChunk;
     return m - m % kDepth;
 }
 
-// round a chunk length up to whole rings
+// round a chunk length up
 inline int round_steps(int sps) { return (sps + kDepth - 1) / kDepth * kDepth; }
 
 // One tile group, in scalars (no arrays: kept in scalar registers on the
-// device).  Slot s of the staged blocks holds input block
-//   diagonal:      rbase + s                       (s < nslots)
-//   off-diagonal:  rbase + s for s < 4, cbase + s - 4 otherwise
-//   halves:        s % 4 (slots 4..7 one step later)
+// device).  Its 128-input groups are
+//   diagonal:      input0, input0 + 128
+//   off-diagonal:  input0 (rows), column0 and column0 + 128
 struct Group {
     int diag;
-    int small;   // the halves geometry
-    int rbase, cbase;
-    int nslots;
+    int input0, column0;
 };
 
 // the halves geometry applies to frames of at most 4 input blocks
@@ -105,30 +111,27 @@ XE_HD inline void offdiag_pair(int ns, int p, int *R, int *C) {
     *C = r + 1 + p;
 }
 
-XE_HD inline Group make_group(int nb, int gid, int halves) {
+XE_HD inline Group make_group(int nb, int gid) {
     Group g;
     int ns = super_rows(nb);
-    g.small = 0;
     if (gid < ns) {
         g.diag = 1;
-        g.small = use_halves(halves, nb);
-        g.rbase = g.cbase = gid * kSuper;
-        g.nslots = kSuper;  // blocks past the last one are staged as zeros
+        g.input0 = gid * kSuper * kBlk;
+        g.column0 = g.input0 + kGroupInputs;
     } else {
         int q = gid - ns;
         int R, C;
         offdiag_pair(ns, q / 2, &R, &C);
         g.diag = 0;
-        g.rbase = R * kSuper + 4 * (q % 2);  // R is never the last super-row
-        g.cbase = C * kSuper;
-        g.nslots = 4 + kSuper;
+        g.input0 = R * kSuper * kBlk + (q % 2) * kGroupInputs;  // R is never the last super-row
+        g.column0 = C * kSuper * kBlk;
     }
     return g;
 }
 
-XE_HD inline int slot_block(const Group &g, int s) {
-    if (g.small) return s & 3;
-    return (g.diag || s < 4) ? g.rbase + s : g.cbase + (s - 4);
+// first input of 128-input group k of a tile group
+XE_HD inline int group_input(const Group &g, int k) {
+    return k == 0 ? g.input0 : g.column0 + (k - 1) * kGroupInputs;
 }
 
 // 32x32 tiles computed per channel: 36 per diagonal group (8 x 9), 32 per

@@ -1,100 +1,136 @@
 // xcorr_kernels.hpp -- gfx950 kernels of the correlator.
 //
 // Correlation (Sec. II-B: cross-correlate every input pair of a channel and
-// add into the previous output):
-//   x = a + i b.  With the real K-vector of one input laid out as the pairs
-//   (a_t, b_t) and the derived vector (b_t, -a_t),
-//     Re V_ij = sum_k Xr_i[k] Xr_j[k]      Im V_ij = sum_k Xp_i[k] Xr_j[k]
-//   with Xr = (a, b), Xp = (b, -a): two real int8 GEMMs with K = 2T on the
-//   matrix cores, exact int32 accumulation.  Only tiles with I <= J run.
-//   A diagonal tile (I = J) is Hermitian, so it runs one GEMM:
-//     Q = Xs Xr^T with Xs = Xr + Xp = (a + b, b - a)  (fits int8),
-//     Re = (Q + Q^T) / 2,  Im = (Q - Q^T) / 2  (exact: Q + Q^T = 2 Re).
+// add into the previous output), on the 6-bit matrix path.
 //
-// A workgroup integrates one tile group (plan.hpp) of one channel over one
-// chunk of time.  Per staged step of 32 samples it
-//   1. loads the packed bytes of its input blocks with dword buffer loads
-//      along the input axis (the buffer range ends at the chunk), kDepth
-//      steps ahead, into a ring of register sets;
-//   2. substitutes 0x88 (= 0) for lost samples, samples past the chunk and
-//      inputs past N, transposes 4x4 byte blocks in registers so that each
-//      dword holds 4 samples of one input, decodes nibbles to signed int8
-//      with carry-free byte arithmetic and writes LDS in the operand layout
-//      of v_mfma_i32_32x32x32_i8: per block and 16-sample sub-step, lane l
-//      reads 16 bytes = 8 samples of input l % 32.  Both operands use the
-//      same K order, so the order of samples inside K does not change the
-//      sum;
-//   3. runs its tiles: A operand (rows) in Xr, Xp (and Xs) form, B Xr.
-// The loop is software-pipelined over three LDS buffers: the decode of step
-// s+2 and the operand reads of step s+1 overlap the MFMAs of step s; one
-// barrier per step; eight waves, two per SIMD, so that one wave's decode
-// and waits overlap the other's MFMAs.
+// A sample is x = a + i b, a = A - 8 and b = B - 8 with the packed nibbles
+// A, B in 0..15.  The 6-bit format E2M3 is linear below 2: code u means u/8
+// for u in 0..15, so a nibble is an operand once its two upper bits are
+// cleared, and bit 5 is the sign.  v_mfma_f32_32x32x64_f8f6f4 runs these at
+// twice the rate of the int8 instruction (7.1 against 3.6 Pop/s, registers
+// only) and takes 6 instead of 8 bits per value from LDS.  Its sums are
+// float32, in units of 1/64: exact while |sum| <= 2^24 units, so a workgroup
+// turns its sums into int32 at least every kSegSteps loop steps (below).
+// With R_ij = sum A_i A_j + B_i B_j and I_ij = sum B_i A_j - A_i B_j over the
+// valid samples, n of them (lost samples are staged as A = B = 0),
+//   Re V_ij = R_ij - 8 (T_i + T_j) + 128 n      T_i = sum A_i + B_i
+//   Im V_ij = I_ij + 8 (D_i - D_j)              D_i = sum A_i - B_i.
+// T and D come from the matrix cores too: one 16x16x128 instruction of a 0/1
+// pattern against an operand sums it for its 32 inputs.
 //
-// Output: chunk 0 of a tile group (or its only chunk) writes its tiles with
-// plain stores (overwrite) or read-add-write (accumulate).  Chunks 1.. store
-// their int32 tiles in the workspace, and merge_kernel, launched next on
-// the same stream, adds them into the output.  Integer sums, so the order of
-// chunks does not matter and the result is exact.
+// Blocks of 32 inputs are strided: block c of a 128-input group holds inputs
+// 4 q + c, q = 0..31.  A dword of the frame is one sample of inputs
+// 4 q .. 4 q + 3, so lane q (and q + 32, for other samples) that loads it
+// holds row q of all four blocks: after a 4x4 byte transpose in registers
+// the operands are complete, with no exchange between lanes.  The order of
+// the samples inside K is arbitrary, but the same for every block.
+//
+// Packing: per 4 samples, three dwords hold (for 4 inputs, a byte each) the
+// bytes of the 24-bit string of four 6-bit codes; a byte transpose of these
+// gives each input's string.  16 samples of one component are 3 dwords; an
+// operand (32 samples of a lane, 64 of the instruction) is 6.
+//
+// Geometries (plan.hpp).  Super: a workgroup of eight waves, two per SIMD,
+// takes a tile group.  Per loop step of 64 samples the waves pack the group's
+// input blocks into LDS, two steps ahead, and run 16 (2 x 2 tiles) or 20 (half
+// the triangle of a 128-input group) matrix instructions each on operands read
+// from LDS; the packing and the reads are woven between them, and while one
+// wave of a SIMD waits the other issues.  Halves (N <= 128): four waves, each
+// packs its own 64 samples of the one group and runs the triangle from
+// registers, without barriers; the waves' sums are added at the end.
+// Short chunks run on another kernel (short_kernels.hpp).
+//
+// What bounds it: 256 inputs, 64 channels, 16,384 samples (four chunks each):
+// a loop step takes 2,080 clocks, of which the matrix instructions fill about
+// 1,280 at the rate above, the packing alone would take about 1,100 issue
+// slots per SIMD, and the hand-over of loaded bytes costs 250; the frame
+// takes 118 us with the merge, where the int8 kernel took 173 (2048 inputs,
+// 16 channels, 8,192 samples: 725 us after 1,004).  One wave per SIMD with
+// 2 x 4 tiles read fewer operands but could not overlap packing with the
+// matrix instructions: 122 against 116 us at 256 inputs x 256 channels x
+// 4,096 samples, 748 against 725 us at 2048 inputs.
+//
+// Diagonal tiles: block c against itself is Hermitian, so one tile
+//   Q = R + I,  R = (Q + Q^T) / 2,  I = (Q - Q^T) / 2  (exact)
+// keeps 16 instead of 32 accumulator registers.
+//
+// Output: chunk 0 of a tile group (or its only chunk) writes its sums with
+// plain stores (overwrite) or read-add-write (accumulate).  Chunks 1.. do the
+// same in a copy of the output in the workspace, and merge_kernel, launched
+// next on the same stream, adds the copies into the output.  Integer sums,
+// so the order of chunks does not matter and the result is exact.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "plan.hpp"
 
 namespace xe {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v3i __attribute__((ext_vector_type(3)));
 typedef int v2i __attribute__((ext_vector_type(2)));
-typedef unsigned v2u __attribute__((ext_vector_type(2)));
+typedef int v6i __attribute__((ext_vector_type(6)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+// four int32 of the output: vis is only 8-byte aligned
+typedef v4i v4i_a8 __attribute__((aligned(8)));
 
-constexpr int kFragBytes = kBlk * kStep * 2;  // one decoded operand of a block per step
-// A diagonal group stages Xr and Xs per block (8 slots x 2 operands), an
-// off-diagonal half stages Xr only (12 slots)
-constexpr int kBufBytes = 16 * kFragBytes;
-// validity bits of a window of steps, one 32-bit word per step
-constexpr int kMaskWindow = 2048;
-// int32 (Re, Im) tiles of one wave in the workspace: 10 tiles x 32 x 64
-constexpr int kWavePartial = kTilesPerWave * 32 * 64;
-constexpr int64_t kGroupPartial = (int64_t)kWaves * kWavePartial;
+// one component of a block per loop step: 64 lanes x 6 dwords, kept as 64 x
+// 16 B (dwords 0..3) and 64 x 8 B (dwords 4, 5)
+constexpr int kCompBytes = 64 * 24;
+constexpr int kHiOff = 64 * 16;
+constexpr int kSlotBytes = 2 * kCompBytes;   // real part, imaginary part
+constexpr int kBufBytes = kMaxSlots * kSlotBytes;
+constexpr int kBufs = 3;
+
+// Exactness: a tile element grows by at most 2 * 15 * 15 = 450 units of 1/64
+// per sample and a Q element by 3 * 15 * 15 = 675, and must stay within
+// 2^24: at most 24,855 samples.
+constexpr int kSegSteps = 384;               // 24,576 samples
+static_assert((int64_t)kSegSteps * kLoop * 675 <= (int64_t)1 << 24, "float32 sums must be exact");
+
+// A triangle's accumulators in LDS: 16 units of 16 registers (Q of block c in
+// unit c, R and I of block pair t in units 4 + 2 t and 5 + 2 t).  Element
+// (row r, column c) of a unit is word
+//   kRowGroup (r / 4) + (r % 4 ^ rotation) + 4 c,
+// so a lane stores 4 registers with 16 bytes.  The output reads a row of the
+// four units of one block together: their rotations differ, so lanes along c
+// meet on no bank, and kRowGroup and kUnit spread lanes along r.
+constexpr int kRowGroup = 4 * kBlk + 4;
+constexpr int kUnit = 8 * kRowGroup + 16;
+constexpr int kDump = 16 * kUnit;
 
 struct CorrArgs {
     const uint8_t *packed;
     const uint8_t *mask;  // may be null
     int32_t *vis;
-    int64_t *count;
-    int32_t *partials;    // [F*groups][splits-1][kGroupPartial] when splits > 1
+    int64_t *count;       // null: counted elsewhere
+    int32_t *partials;    // [splits - 1][partial_stride] when splits > 1
+    int64_t partial_stride;
     int N, F, T, B;
     int nblk_mask;        // ceil(T / B)
     int nb;               // ceil(N / 32)
     int groups;           // groups per channel
     int splits;
-    int steps_per_split;
-    int halves;           // the halves geometry when N <= 128
+    int steps_per_split;  // 32-sample steps
+    int overwrite;
 };
 
 // ---------------------------------------------------------------------------
-// byte tricks (all carry-free per byte)
+// packing
 // ---------------------------------------------------------------------------
-
-// nibble u in 0..15 per byte -> u - 8 as int8: (u + 0x78) ^ 0x80
-__device__ __forceinline__ uint32_t nib_to_s8(uint32_t u) {
-    return (u + 0x78787878u) ^ 0x80808080u;
-}
-
-// -x per byte for x in [-8, 7]: ((x ^ 0x7f) + 1) ^ 0x80, no byte overflows
-__device__ __forceinline__ uint32_t neg_s8(uint32_t x) {
-    return ((x ^ 0x7f7f7f7fu) + 0x01010101u) ^ 0x80808080u;
-}
 
 __device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
     return __builtin_amdgcn_perm(hi, lo, sel);
 }
 
-// 4x4 byte transpose: d[e] holds inputs 0..3 of sample e; out[c] holds
-// samples 0..3 of input c
-__device__ __forceinline__ void transpose4(const uint32_t d[4], uint32_t out[4]) {
+// 4x4 byte transpose: out[c] = bytes c of d[0..3]
+__device__ __forceinline__ void transpose4(const uint32_t *d, uint32_t out[4]) {
     uint32_t e0 = perm(d[1], d[0], 0x05010400u);  // d00 d10 d01 d11
     uint32_t e1 = perm(d[1], d[0], 0x07030602u);  // d02 d12 d03 d13
     uint32_t e2 = perm(d[3], d[2], 0x05010400u);  // d20 d30 d21 d31
@@ -105,135 +141,278 @@ __device__ __forceinline__ void transpose4(const uint32_t d[4], uint32_t out[4])
     out[3] = perm(e3, e1, 0x07060302u);
 }
 
-// 4 validity bits -> 4 byte masks (0xff = valid)
-__device__ __forceinline__ uint32_t bits_to_bytes(uint32_t b4) {
-    uint32_t m = (b4 * 0x00204081u) & 0x01010101u;  // bit k -> byte k
-    return (m << 8) - m;
+// One component of 4 samples (d[e] = sample e of 4 inputs, a byte each) as
+// the three bytes of four 6-bit codes, per input:
+//   byte 0 = n0 | n1 << 6,  byte 1 = n1 >> 2 | n2 << 4,  byte 2 = n3 << 2
+template <bool kRe>
+__device__ __forceinline__ void pack4(const uint32_t *d, uint32_t *o) {
+    if (kRe) {  // high nibbles
+        o[0] = ((d[0] >> 4) & 0x0f0f0f0fu) | ((d[1] << 2) & 0xc0c0c0c0u);
+        o[1] = ((d[1] >> 6) & 0x03030303u) | (d[2] & 0xf0f0f0f0u);
+        o[2] = (d[3] >> 2) & 0x3c3c3c3cu;
+    } else {
+        o[0] = (d[0] & 0x0f0f0f0fu) | ((d[1] << 6) & 0xc0c0c0c0u);
+        o[1] = ((d[1] >> 2) & 0x03030303u) | ((d[2] << 4) & 0xf0f0f0f0u);
+        o[2] = (d[3] << 2) & 0x3c3c3c3cu;
+    }
 }
 
-// A 16-byte operand chunk holds, for 8 samples of one input,
-// (a0..3 | b0..3 | a4..7 | b4..7).  Xr chunk -> Xp chunk (b | -a).
-__device__ __forceinline__ v4i make_xp(v4i x) {
-    v4i p;
-    p.x = x.y;
-    p.y = (int)neg_s8((uint32_t)x.x);
-    p.z = x.w;
-    p.w = (int)neg_s8((uint32_t)x.z);
-    return p;
-}
-
-__device__ __forceinline__ v16i mfma(v4i a, v4i b, v16i c) {
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
-}
-
-// LDS position of the 16-byte chunk c (= lane-group g * 32 + row r) of
-// (block slot s, operand op, sub-step u).  The 64 chunks of one (s, op, u)
-// form 1 KB; lane l of a reading wave takes chunk l, stored at
-//   phys(l, s) = l ^ (s & 1) ^ (bit 4 of l) << 1,
-// a permutation inside aligned groups of 4 chunks, so a wave's 16-byte
-// reads stay conflict-free while the stagers' 8-byte writes (below) hit all
-// 64 banks exactly once per half-wave.
-__device__ __forceinline__ int phys_chunk(int c, int s) {
-    return c ^ (s & 1) ^ (((c >> 4) & 1) << 1);
-}
-__device__ __forceinline__ int chunk_off(int slot_bytes, int s, int op, int u, int c) {
-    return s * slot_bytes + op * kFragBytes + u * 1024 + (phys_chunk(c, s) << 4);
-}
-
-// ---------------------------------------------------------------------------
-// staging: global packed bytes -> decoded int8 operand layout in LDS
-// ---------------------------------------------------------------------------
-
-// One staging unit = 4 inputs (n0..n0+3) x 4 samples (sample quad sq of the
-// step) of block slot s.  Units come in rounds of 64 per wave: lane bits
-// (q = lane & 7, s_lo = bit 3, h = bit 4, s_hi = bit 5) give input quad q,
-// slot 4 sg + s_lo + 2 s_hi and sample quad 2 o + h, with the octet o and
-// the slot group sg fixed per wave-round.  Coordinates do not change along
-// the time loop.
-struct Unit {
-    int s, q, sq;
-    uint32_t voff;  // byte offset of (sample 4 sq, input n0) within the chunk;
-                    // out of range (reads 0) when the inputs lie past N
-    bool act;       // inputs lie below N (else staged as 0)
-    bool hi;        // halves geometry, slots 4..7: the odd step of the pair
-    uint32_t inb;   // unaligned path: byte c of the dword lies below N
+// A half-unit: 16 samples of 4 inputs per lane (lanes 0..31: samples 0..15 of
+// a 32-sample step, lanes 32..63: samples 16..31).  A component is packed in pieces of about 8
+// vector instructions, which the loops place between matrix instructions: pack<kRe, g> for each 4 samples,
+// then transpose<k>, k = 0..2, after which w[c] are the 3 dwords of input
+// c.  (The asm: computed there, and not moved to where the result is used.)
+struct Packer {
+    uint32_t x[12];
+    v3i w[4];
+    template <bool kRe, int G>
+    __device__ __forceinline__ void pack(const uint32_t (&raw)[16]) {
+        uint32_t *o = x + 3 * G;
+        pack4<kRe>(raw + 4 * G, o);
+        asm volatile("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]));
+    }
+    template <int K>
+    __device__ __forceinline__ void transpose() {
+        uint32_t t[4];
+        transpose4(x + 4 * K, t);
+        asm volatile("" : "+v"(t[0]), "+v"(t[1]), "+v"(t[2]), "+v"(t[3]));
+        w[0][K] = (int)t[0];
+        w[1][K] = (int)t[1];
+        w[2][K] = (int)t[2];
+        w[3][K] = (int)t[3];
+    }
+    // dwords 3 p .. 3 p + 2 of the component in LDS, dst = slot of input 0's
+    // block, component and lane 0
+    template <int C>
+    __device__ __forceinline__ void write_first(uint8_t *d) const {
+        if constexpr (C < 4) {
+            *(v3i *)(d + C * kSlotBytes) = w[C];
+            write_first<C + 1>(d);
+        }
+    }
+    template <int C>
+    __device__ __forceinline__ void write_second(uint8_t *d, uint8_t *e) const {
+        if constexpr (C < 4) {
+            *(int *)(d + C * kSlotBytes) = w[C].x;
+            *(v2i *)(e + C * kSlotBytes) = w[C].yz;
+            write_second<C + 1>(d, e);
+        }
+    }
+    __device__ __forceinline__ void write(uint8_t *dst, int p, int lane) const {
+        if (p == 0)
+            write_first<0>(dst + lane * 16);
+        else
+            write_second<0>(dst + lane * 16 + 12, dst + kHiOff + lane * 8);
+    }
+    // the same into operands held in registers
+    template <int P, int E>
+    __device__ __forceinline__ void keep(v6i (&x)[4]) const {
+        if constexpr (E < 12) {
+            int t = w[E / 3][E % 3];
+            asm volatile("" : "+v"(t));   // (else both arrays stay in memory)
+            x[E / 3][3 * P + E % 3] = t;
+            keep<P, E + 1>(x);
+        }
+    }
 };
 
-template <int UPT>
-struct Prefetch {
-    uint32_t d[UPT][4];
-};
+// sign flips of 6-bit codes in an operand (bit 5 of every code)
+__device__ __forceinline__ v6i negate(v6i x) {
+    constexpr int k0 = 0x20820820, k1 = 0x08208208, k2 = (int)0x82082082u;
+    return x ^ (v6i){k0, k1, k2, k0, k1, k2};
+}
 
-// The chunk of a workgroup: samples [t_begin, t_end) of channel f, read
-// through a buffer resource whose range ends at the last byte of the chunk,
-// so every load is bounds-checked by the hardware (reads past it return 0;
-// such samples are replaced below anyway).
+__device__ __forceinline__ v8i wide(v6i x) {
+    return __builtin_shufflevector(x, x, 0, 1, 2, 3, 4, 5, -1, -1);
+}
+
+__device__ __forceinline__ v16f mfma(v6i a, v6i b, v16f c) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(wide(a), wide(b), c, 2, 2, 0, 0, 0, 0);
+}
+
+// Input sums of an operand: rows of a 0/1 pattern (4-bit codes, 2 = 1.0).  In
+// the 16x16x128 instruction lane l of the pattern is row l % 16, and of an
+// operand column l % 16, both at K quarter l / 16; the operand's lanes l and
+// l + 32 belong to input l % 32, so quarters 0 and 2 are inputs 0..15, 1 and 3
+// inputs 16..31.  Pattern of the real part: row 0 = quarters 0, 2 and row 1
+// = quarters 1, 3; of the imaginary part: rows 2 and 3.  Lane c < 16 of the
+// result then holds (sum A, sum A', sum B, sum B') / 8 of inputs c and
+// c + 16.
+__device__ __forceinline__ v4i sum_pattern(bool im, int lane) {
+    const int row = lane & 15, odd = (lane >> 4) & 1;
+    const int x = row == (im ? 2 : 0) + odd ? 0x22222222 : 0;
+    return (v4i){x, x, x, x};
+}
+
+// Inline asm, because the four accumulators have to live in ordinary
+// registers: the tiles take every AGPR, and the compiler gives the builtin's
+// only those, at 8 register moves per instruction (a third of a step's issue
+// slots).  The compiler does not know the instruction's latency, so its
+// result must not be touched for 20 wait states: every use below follows it
+// by at least 8 of the 32-cycle tile instructions, or by a barrier.
+__device__ __forceinline__ void sum_mfma(v4i pat, v6i b, v4f &c) {
+    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:4 blgp:2"
+                 : "+v"(c)
+                 : "v"(pat), "v"(b));
+}
+
+__device__ __forceinline__ int units(float x) { return (int)(x * 64.0f); }
+
+// ---------------------------------------------------------------------------
+// loads
+// ---------------------------------------------------------------------------
+
+// The chunk of a workgroup: samples [t_begin, t_end) of channel f.  Loads go
+// through a buffer resource whose range ends with the last dword of the
+// chunk's last row, so every dword is checked by the hardware and reads 0
+// past it.  All members are wave-uniform.
+// Inputs past N (lanes of the last group) read the next channel's bytes or 0;
+// their products are never stored.  Only the frame's end may cut a dword off
+// (N % 4 != 0): see Tail.
 struct Chunk {
-    __amdgpu_buffer_rsrc_t rsrc;
-    uint32_t row_bytes;  // F * N: bytes between consecutive samples
+    uint64_t base;   // address of (t_begin, f, input 0)
+    uint32_t row;    // F * N: bytes between consecutive samples
+    int extent;      // bytes from base that may be read, < 2^31
     int t_begin, t_end;
 };
 
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
 __device__ __forceinline__ Chunk make_chunk(const CorrArgs &a, int f, int t_begin, int t_end) {
     Chunk c;
-    // every value here is wave-uniform; readfirstlane keeps the resource in
-    // scalar registers (a buffer load needs it there)
-    uint64_t base = (uint64_t)(uintptr_t)(a.packed + ((int64_t)t_begin * a.F + f) * a.N);
-    uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-    uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-    uint32_t row = __builtin_amdgcn_readfirstlane((uint32_t)a.F * (uint32_t)a.N);
-    uint32_t extent = __builtin_amdgcn_readfirstlane((uint32_t)(t_end - t_begin - 1) * row +
-                                                     (uint32_t)a.N);
-    void *p = (void *)(uintptr_t)(((uint64_t)hi << 32) | lo);
-    c.rsrc = __builtin_amdgcn_make_buffer_rsrc(p, (short)0, (int)extent, 0x00020000);
-    c.row_bytes = row;
+    const uint64_t base =
+        (uint64_t)(uintptr_t)(a.packed + ((int64_t)t_begin * a.F + f) * a.N);
+    c.base = ((uint64_t)uniform((uint32_t)(base >> 32)) << 32) | uniform((uint32_t)base);
+    c.row = uniform((uint32_t)a.F * (uint32_t)a.N);
+    const int64_t rows = (int64_t)(t_end - t_begin - 1) * c.row;
+    const int64_t left = ((int64_t)(a.T - 1 - t_begin) * a.F + (a.F - 1 - f)) * a.N + a.N;
+    const int64_t want = rows + (a.N + 3) / 4 * 4;
+    c.extent = (int)uniform((uint32_t)(want < left ? want : left));
     c.t_begin = t_begin;
     c.t_end = t_end;
     return c;
 }
 
-// The whole byte offset goes into the vector offset, which the hardware
-// checks against the resource's range (loads past the chunk read 0); the
-// scalar offset stays 0.  Offsets stay below 2^31 (the host bounds a
-// chunk, its lookahead included), so an inactive unit's 0x80000000 stays
-// out of range.
-template <bool kAligned, int UPT>
-__device__ __forceinline__ void issue_loads(const Chunk &ch, int tb, const Unit (&u)[UPT],
-                                            Prefetch<UPT> &p) {
-    const uint32_t step_off = (uint32_t)(tb - ch.t_begin) * ch.row_bytes;
+// The chunk from `skip` bytes on (whole rows plus a group's first input).
+// skip stays below 2^32, the lookahead past a chunk included.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const Chunk &ch, uint32_t skip) {
+    uint64_t p = ch.base + skip;
+    p = ((uint64_t)uniform((uint32_t)(p >> 32)) << 32) | uniform((uint32_t)p);
+    const int left = skip < (uint32_t)ch.extent ? (int)((uint32_t)ch.extent - skip) : 0;
+    return __builtin_amdgcn_make_buffer_rsrc((void *)(uintptr_t)p, (short)0,
+                                             (int)uniform((uint32_t)left), 0x00020000);
+}
+
+// A half-unit (32 samples of a 128-input group) is loaded as 4 x 16 bytes per
+// lane, piece k = samples 8 k .. 8 k + 7, kept in registers for two loop steps
+// and then put into LDS as rows of 128 bytes, from which the lanes read their
+// dwords.  Loading the dwords themselves (one sample of 4 inputs per lane)
+// costs an address cycle per quad of lanes: 23 bytes per ns and CU against 72
+// with 16-byte loads, less than the matrix cores take in.  Rows 16..31 lie
+// 128 bytes further, on the other 32 banks.  The loads may have any byte
+// alignment.
+constexpr uint32_t kNowhere = 0x80000000u;   // an offset out of every range
+constexpr int kRawBytes = 32 * kGroupInputs + 128;
+
+__device__ __forceinline__ void raw_offsets(uint32_t (&voff)[4], uint32_t row, int lane) {
 #pragma unroll
-    for (int r = 0; r < UPT; ++r) {
+    for (int k = 0; k < 4; ++k)
+        voff[k] = (uint32_t)(8 * k + (lane >> 3)) * row + 16 * (uint32_t)(lane & 7);
+}
+
+template <int kFrom, int kTo>
+__device__ __forceinline__ void load_raw(__amdgpu_buffer_rsrc_t r, const uint32_t (&voff)[4],
+                                         v4i (&d)[kTo - kFrom]) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const uint32_t off = u[r].voff + step_off + (uint32_t)e * ch.row_bytes;
-            if (kAligned) {
-                p.d[r][e] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(ch.rsrc, (int)off, 0, 0);
-            } else {
-                uint32_t v = 0;
+    for (int k = kFrom; k < kTo; ++k)
+        d[k - kFrom] = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff[k], 0, 0);
+}
+
+// The end of the frame when N % 4 != 0: the dword of inputs that straddles N
+// is out of range in the channel's last row where the frame ends within it
+// (and in up to two rows more when F * N < 4).  These dwords are assembled
+// from bytes once per segment, into LDS, and replace the loaded ones.
+constexpr int kMaxCut = 3;
+struct Tail {
+    int last;   // last sample of the frame, from the segment's first
+    int cut;    // rows whose dword is cut off
+};
+
+// Threads 0 .. cut - 1 fill tails[k] = the dword of row T - 1 - k.
+__device__ __forceinline__ Tail make_tail(const CorrArgs &a, int f, int t_seg, uint32_t *tails) {
+    Tail t;
+    t.last = a.T - 1 - t_seg;
+    t.cut = 0;
+    if (a.N % 4 == 0) return t;
+    for (int k = 0; k < kMaxCut && k < a.T; ++k)
+        t.cut += (int64_t)(k * a.F + a.F - f) * a.N < (a.N + 3) / 4 * 4 ? 1 : 0;
+    const int k = threadIdx.x, n0 = a.N / 4 * 4;
+    if (k < t.cut) {
+        const uint8_t *p = a.packed + ((int64_t)(a.T - 1 - k) * a.F + f) * a.N;
+        uint32_t x = 0;
+        for (int c = 0; n0 + c < a.N; ++c) x |= (uint32_t)p[n0 + c] << (8 * c);
+        tails[k] = x;
+    }
+    return t;
+}
+
+// Pieces kFrom .. kTo - 1 of a half-unit (32-sample step `word` of the segment,
+// validity `bits`, first input input0) into LDS: lost samples zeroed, cut
+// rows replaced.
+template <int kFrom, int kTo>
+__device__ __forceinline__ void store_raw(uint8_t *raw, v4i (&d)[kTo - kFrom], uint32_t bits,
+                                          int word, const Tail &t, const uint32_t *tails, int N,
+                                          int input0, int lane) {
+    if (bits != 0xffffffffu) {
+        const int mine = (int)(bits >> (lane >> 3));
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    uint32_t b = (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(
-                        ch.rsrc, (int)(off + c), 0, 0);
-                    v |= (((u[r].inb >> c) & 1u) ? b : 0x88u) << (8 * c);
-                }
-                p.d[r][e] = v;
-            }
+        for (int k = kFrom; k < kTo; ++k) {
+            const int m = __builtin_amdgcn_sbfe(mine, 8 * k, 1);
+            d[k - kFrom] &= (v4i){m, m, m, m};
         }
+    }
+#pragma unroll
+    for (int k = kFrom; k < kTo; ++k)
+        *(v4i *)(raw + 1024 * k + (k >= 2 ? 128 : 0) + 16 * lane) = d[k - kFrom];
+    const int n0 = N / 4 * 4 - input0;   // the straddling dword's byte in a row
+    if (t.cut > 0 && n0 >= 0 && n0 < kGroupInputs &&
+        (word == t.last >> 5 || word == (t.last - t.cut + 1) >> 5)) {
+        const int row = t.last - lane - 32 * word;
+        if (lane < t.cut && row >= 8 * kFrom && row < 8 * kTo)
+            *(uint32_t *)(raw + 128 * row + (row >= 16 ? 128 : 0) + n0) =
+                (bits >> row) & 1u ? tails[lane] : 0u;
     }
 }
 
-// Validity words of steps [s0, s0 + kMaskWindow) of the chunk into LDS: bit k
-// of word s = sample t_begin + 32 s + k lies inside the chunk and not in a
-// lost block.  All threads take part; call between barriers.
-__device__ inline void fill_mask_window(const CorrArgs &a, int f, const Chunk &ch, int s0,
-                                        int nsteps, uint32_t *words) {
+// a lane's 16 rows (16 (lane / 32) .. + 15)
+__device__ __forceinline__ void read_raw(const uint8_t *raw, int lane, uint32_t (&r)[16]) {
+    const uint8_t *p = raw + (lane >> 5) * (16 * 128 + 128) + 4 * (lane & 31);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) r[e] = *(const uint32_t *)(p + 128 * e);
+}
+
+// Keeps what is computed from x (output addresses) from being moved ahead of
+// the main loop, where it would take the loop's registers.
+__device__ __forceinline__ int keep_late(int x) {
+    asm volatile("" : "+v"(x));
+    return x;
+}
+
+// n validity words of the samples from t0 on: bit k of word w = sample
+// t0 + 32 w + k lies before t1 and not in a lost block.  All threads take
+// part; returns the valid samples of the words this thread wrote.
+template <int kThreads>
+__device__ inline int fill_words(const CorrArgs &a, int f, int t0, int t1, int n,
+                                 uint32_t *words) {
     const uint8_t *m = a.mask ? a.mask + (int64_t)f * a.nblk_mask : nullptr;
-    const int n = (nsteps - s0) < kMaskWindow ? (nsteps - s0) : kMaskWindow;
+    int valid = 0;
     for (int w = threadIdx.x; w < n; w += kThreads) {
-        const int tb = ch.t_begin + (s0 + w) * kStep;
-        const int left = ch.t_end - tb;
-        uint32_t bits = left >= 32 ? 0xffffffffu : ((1u << left) - 1u);
-        if (m) {
+        const int tb = t0 + 32 * w;
+        const int left = t1 - tb;
+        uint32_t bits = left >= 32 ? 0xffffffffu : left > 0 ? (1u << left) - 1u : 0u;
+        if (m && left > 0) {
             int blk = tb / a.B;
             for (int k0 = blk * a.B - tb; k0 < 32 && blk < a.nblk_mask; k0 += a.B, ++blk) {
                 if (m[blk]) {
@@ -246,312 +425,987 @@ __device__ inline void fill_mask_window(const CorrArgs &a, int f, const Chunk &c
             }
         }
         words[w] = bits;
+        valid += __popc(bits);
+    }
+    return valid;
+}
+
+// ---------------------------------------------------------------------------
+// output
+// ---------------------------------------------------------------------------
+
+// Where a workgroup's sums of one channel go, and how: the output itself
+// (chunk 0) or the chunk's copy of it in the workspace.  Accesses go through a
+// buffer resource over the channel's sums, and elements that are not to be
+// written have an offset out of its range: without branches around them the
+// compiler can tell how many accesses are in flight, and loads of old sums
+// need not wait for the stores before them.
+struct Dest {
+    __amdgpu_buffer_rsrc_t rsrc;   // [P][2] of the channel, P * 8 < 2^27 bytes
+    bool add;
+};
+
+__device__ __forceinline__ Dest make_dest(const CorrArgs &a, int f, int split, bool first_seg) {
+    const int64_t P = (int64_t)a.N * (a.N + 1) / 2;
+    const int32_t *out =
+        (split == 0 ? a.vis : a.partials + (int64_t)(split - 1) * a.partial_stride) +
+        (int64_t)f * P * 2;
+    const uint64_t p = (uint64_t)(uintptr_t)out;
+    Dest d;
+    d.rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(uintptr_t)(((uint64_t)uniform((uint32_t)(p >> 32)) << 32) | uniform((uint32_t)p)),
+        (short)0, (int)uniform((uint32_t)P * 8), 0x00020000);
+    d.add = !first_seg || (split == 0 && !a.overwrite);
+    return d;
+}
+
+// byte offset of (i, j) in the packed triangle
+__device__ __forceinline__ uint32_t tri_bytes(int N, int i, int j) {
+    return 4u * (uint32_t)(i * (2 * N - i + 1)) + 8u * (uint32_t)(j - i);
+}
+
+// which word of its four a row takes: r % 4 ^ rotation (of a pair, c ^ c')
+__device__ constexpr int unit_rotation(int u) {
+    constexpr int pair[6] = {1, 2, 3, 3, 2, 1};
+    return u < 4 ? 0 : pair[(u - 4) / 2];
+}
+
+// registers of unit U into a dump (kAdd: added to it)
+template <bool kAdd, int U>
+__device__ __forceinline__ void put_unit(float *dump, const v16f &acc, int lane) {
+    constexpr int x = unit_rotation(U);
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {   // rows 8 g + 4 (lane / 32) .. + 3
+        v4f *d = (v4f *)(dump + U * kUnit + (2 * g + (lane >> 5)) * kRowGroup + 4 * (lane & 31));
+        v4f y = {acc[4 * g + (0 ^ x)], acc[4 * g + (1 ^ x)], acc[4 * g + (2 ^ x)],
+                 acc[4 * g + (3 ^ x)]};
+        if (kAdd) y += *d;
+        *d = y;
+    }
+}
+template <bool kAdd, int U>
+__device__ __forceinline__ void put_triangle(float *dump, const v16f (&acc)[16], int lane) {
+    if constexpr (U < 16) {
+        put_unit<kAdd, U>(dump, acc[U], lane);
+        put_triangle<kAdd, U + 1>(dump, acc, lane);
     }
 }
 
-// Decode one prefetched step into LDS (validity words vb0 for its units, vb1
-// for the odd-step units of the halves geometry).  Per input, from the
-// masked nibbles
-// A' = a + 8 and B' = b + 8 (4 samples per dword):
-//   Xr = (a | b)             a = (A' + 0x78) ^ 0x80
-//   Xs = (a + b | b - a)     a + b = (A' + B' + 0x70) ^ 0x80,
-//                            b - a = ((B' | 0x80) - A') ^ 0x80
-// all per byte without carries or borrows; Xs only for diagonal groups.
-// A unit writes bytes 8h .. 8h+7 of its inputs' chunks (h = sq & 1).
-template <bool kXs, bool kSmall, int UPT>
-__device__ __forceinline__ void commit(const Unit (&u)[UPT], const Prefetch<UPT> &p,
-                                       uint32_t vb0, uint32_t vb1, uint8_t *buf,
-                                       int slot_bytes) {
+// Output rows of the triangle of one 128-input group (first input in0) from
+// its dump: rows 4 q + ci for q = q0, q0 + dq, ... < q1 and every ci; lane l
+// takes columns l and l + 64.  A lane reads two words x, y per element and
+// gets R and I as linear combinations: for ci < cj (cj = l % 4) x, y = R, I of
+// the pair's element (q, q'), for ci > cj those of (q', q), conjugated, and on
+// a diagonal tile x, y = Q, Q^T.  Where a row's words lie differs between
+// lanes only in whether the row steps along r or along c.  Batches of kRows
+// rows, with the old sums of the next one (kAdd) requested before this one's
+// are stored.
+template <bool kAdd, int kRows>
+__device__ __forceinline__ void write_triangle_as(const float *dump, const v2i *sums,
+                                                  int valid128, int in0, int N,
+                                                  __amdgpu_buffer_rsrc_t out, int q0, int q1,
+                                                  int dq, int lane) {
+    const int rows = N - in0 < kGroupInputs ? N - in0 : kGroupInputs;
+    const int cj = lane & 3, qj = lane >> 2;
+    v2i sj[2];
+    sj[0] = sums[cj * kBlk + qj];
+    sj[1] = sums[cj * kBlk + qj + 16];
+    sj[0].x = valid128 - sj[0].x;
+    sj[1].x = valid128 - sj[1].x;
+    const int batches = (q1 - q0 + kRows * dq - 1) / (kRows * dq);
+    auto offset = [&](int b, int r, int s) -> uint32_t {
+        const int ci = b / batches, q = q0 + (b % batches * kRows + r) * dq;
+        const int i = 4 * q + ci, j = 64 * s + lane;
+        const uint32_t at = tri_bytes(N, in0 + i, in0 + j);
+        return q < q1 && i < rows && j >= i && j < rows ? at : kNowhere;
+    };
+    v2i old[kRows][2];
+    auto load_old = [&](int b) {
 #pragma unroll
-    for (int r = 0; r < UPT; ++r) {
-        uint32_t L[4];
-        transpose4(p.d[r], L);
-        const uint32_t vbits = kSmall && u[r].hi ? vb1 : vb0;
-        const uint32_t vq = u[r].act ? (vbits >> (4 * u[r].sq)) & 15u : 0u;
-        const uint32_t m = bits_to_bytes(vq);
-        const int o = u[r].sq >> 1, h = u[r].sq & 1;
+        for (int r = 0; r < kRows; ++r)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            uint32_t Lm = (L[c] & m) | (0x88888888u & ~m);
-            uint32_t an = (Lm >> 4) & 0x0f0f0f0fu, bn = Lm & 0x0f0f0f0fu;
-            uint8_t *dst = buf + chunk_off(slot_bytes, u[r].s, 0, o >> 1,
-                                           (o & 1) * 32 + 4 * u[r].q + c) + 8 * h;
-            v2u xr = {nib_to_s8(an), nib_to_s8(bn)};
-            *(v2u *)dst = xr;
-            if (kXs) {
-                v2u xs = {(an + bn + 0x70707070u) ^ 0x80808080u,
-                          ((bn | 0x80808080u) - an) ^ 0x80808080u};
-                *(v2u *)(dst + kFragBytes) = xs;
+            for (int s = 0; s < 2; ++s)
+                old[r][s] = __builtin_amdgcn_raw_buffer_load_b64(out, (int)offset(b, r, s), 0, 0);
+    };
+    if (kAdd) load_old(0);
+#pragma clang loop unroll(disable)
+    for (int b = 0; b < 4 * batches; ++b) {
+        const int ci = b / batches, qb = q0 + b % batches * kRows * dq;
+        const bool q = ci == cj, t = ci > cj;   // diagonal tile, transposed pair
+        const int lo = t ? cj : ci, hi = t ? ci : cj;
+        const int pair = lo == 0 ? hi - 1 : lo + hi;   // 01 02 03 12 13 23
+        const int ux = q ? ci : 4 + 2 * pair, uy = q ? ci : 5 + 2 * pair;
+        const bool ty = q || t;                         // y is read along c
+        const int rot = ci ^ cj, col = 4 * qj;
+        const int trans = kRowGroup * (qj >> 2) + ((qj & 3) ^ rot);
+        const float *px = dump + ux * kUnit + (t ? trans : col);
+        const float *py = dump + uy * kUnit + (ty ? trans : col);
+        // 16 columns further: 4 row groups, or 64 words
+        const int dx = t ? 4 * kRowGroup : 64, dy = ty ? 4 * kRowGroup : 64;
+        const float rx = q ? 32.0f : 64.0f, ry = q ? 32.0f : 0.0f;
+        const float ix = q ? 32.0f : 0.0f, iy = q ? -32.0f : t ? -64.0f : 64.0f;
+        float u[kRows][2], w[kRows][2];
+        v2i si[kRows];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r) {
+            const int qi = qb + r * dq < kBlk ? qb + r * dq : 0;
+            const int along_r = kRowGroup * (qi >> 2) + ((qi & 3) ^ rot), along_c = 4 * qi;
+            const float *ax = px + (t ? along_c : along_r), *ay = py + (ty ? along_c : along_r);
+            si[r] = sums[ci * kBlk + qi];
+            u[r][0] = ax[0];
+            u[r][1] = ax[dx];
+            w[r][0] = ay[0];
+            w[r][1] = ay[dy];
+        }
+        v2i x[kRows][2];
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                x[r][s].x = (int)__builtin_fmaf(w[r][s], ry, u[r][s] * rx) + sj[s].x - si[r].x;
+                x[r][s].y = (int)__builtin_fmaf(w[r][s], iy, u[r][s] * ix) - sj[s].y + si[r].y;
+                if (kAdd) x[r][s] += old[r][s];
             }
+        if (kAdd && b + 1 < 4 * batches) load_old(b + 1);
+#pragma unroll
+        for (int r = 0; r < kRows; ++r)
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+                __builtin_amdgcn_raw_buffer_store_b64(x[r][s], out, (int)offset(b, r, s), 0, 0);
+    }
+}
+
+template <int kRows>
+__device__ __forceinline__ void write_triangle(const float *dump, const v2i *sums, int valid128,
+                                               int in0, int N, const Dest &d, int q0, int q1,
+                                               int dq, int lane) {
+    if (d.add)
+        write_triangle_as<true, kRows>(dump, sums, valid128, in0, N, d.rsrc, q0, q1, dq, lane);
+    else
+        write_triangle_as<false, kRows>(dump, sums, valid128, in0, N, d.rsrc, q0, q1, dq, lane);
+}
+
+// ---------------------------------------------------------------------------
+// super geometry
+// ---------------------------------------------------------------------------
+
+// Roles of the eight waves of a group (waves w and w + 4 share a SIMD).
+// Diagonal: waves 0..3 take 2 x 2 tiles of the first 128-input group against
+// the second, waves 4, 5 (6, 7) the two halves of the triangle of the first
+// (second) group; waves w and w + 4 pack the real and the imaginary part of one
+// half-unit.  Off-diagonal half: every wave takes 2 x 2 tiles, rows 2 (w % 2),
+// + 1 and columns 2 (w / 2), + 1; waves 0..3 pack a half-unit of the column
+// groups each, waves 4..7 a component of one of the row group.
+enum Role { kDiagRect = 0, kTriA = 1, kTriB = 2, kOffFull = 3, kOffRe = 4, kOffIm = 5 };
+
+struct SuperLds {
+    union {
+        struct {
+            uint8_t stage[kBufs * kBufBytes];
+            // diagonal: [step parity][half-unit]; off-diagonal: 0..3 the next
+            // step of waves 0..3, 4 + [step parity][32-sample step] the rows
+            uint8_t raw[8][kRawBytes];
+        };
+        float dump[2][kDump];
+    };
+    uint32_t words[2 * kSegSteps];
+    v2i sums[kMaxSlots * kBlk];   // (8 T, 8 D) of input 4 q + c at [slot][q]
+    uint32_t tails[kMaxCut];
+    int valid;
+};
+static_assert(sizeof(SuperLds) <= 160 * 1024, "LDS of a compute unit");
+
+// Matrix instruction M (0..19) of half a triangle's loop step.  Tiles of half
+// A: Q0, Q1 and pairs 01 02 03; of half B: Q2, Q3 and 12 13 23, as acc[0, 1]
+// and (re, im) in acc[2 ..].  0..4: A against A, 5..9: B rows against A
+// columns, 10..14: -A rows against B, 15..19: B against B.  A block of A is
+// negated after its last use as a column.
+struct TriOp {
+    int row, col, acc;
+};
+template <bool kHalfB>
+__device__ constexpr TriOp tri_op(int m) {
+    constexpr TriOp a[20] = {{0, 0, 0}, {0, 1, 2}, {1, 1, 1}, {0, 2, 4}, {0, 3, 6},
+                             {0, 0, 0}, {0, 1, 3}, {1, 1, 1}, {0, 2, 5}, {0, 3, 7},
+                             {0, 0, 0}, {0, 1, 3}, {0, 2, 5}, {0, 3, 7}, {1, 1, 1},
+                             {0, 0, 0}, {0, 1, 2}, {0, 2, 4}, {0, 3, 6}, {1, 1, 1}};
+    constexpr TriOp b[20] = {{1, 2, 2}, {1, 3, 4}, {2, 2, 0}, {2, 3, 6}, {3, 3, 1},
+                             {1, 2, 3}, {2, 2, 0}, {1, 3, 5}, {2, 3, 7}, {3, 3, 1},
+                             {1, 2, 3}, {1, 3, 5}, {2, 2, 0}, {2, 3, 7}, {3, 3, 1},
+                             {1, 2, 2}, {1, 3, 4}, {2, 2, 0}, {2, 3, 6}, {3, 3, 1}};
+    return kHalfB ? b[m] : a[m];
+}
+// dump unit of acc[k]
+template <bool kHalfB>
+__device__ constexpr int tri_unit(int k) {
+    return kHalfB ? (k < 2 ? 2 + k : 8 + k) : (k < 2 ? k : 2 + k);
+}
+
+__device__ __forceinline__ v6i read_op(const uint8_t *comp, int lane) {
+    const v4i x = *(const v4i *)(comp + lane * 16);
+    const v2i y = *(const v2i *)(comp + kHiOff + lane * 8);
+    return (v6i){x.x, x.y, x.z, x.w, y.x, y.y};
+}
+
+template <int ROLE>
+struct SuperWave {
+    static constexpr bool kTri = ROLE == kTriA || ROLE == kTriB, kHalfB = ROLE == kTriB;
+    static constexpr bool kOff = ROLE >= kOffFull;
+    static constexpr int kOps = kTri ? 20 : 16;
+    // pieces of packing per step, 8 per component
+    static constexpr int kAll = ROLE == kOffFull ? 16 : 8;
+    static constexpr bool kRe = ROLE == kDiagRect || ROLE == kOffRe;   // (of one component)
+    // the first piece (its rows are read after matrix instruction 0), and the
+    // end, by which the last piece lands before the barrier
+    static constexpr int kLead = 2, kSpan = kOps - 1;
+    // 16-byte pieces of its half-unit that the wave loads
+    static constexpr int kFrom = ROLE == kOffFull || kRe ? 0 : 2;
+    static constexpr int kTo = ROLE == kOffFull ? 4 : kFrom + 2;
+    static constexpr int kSets = ROLE == kOffFull ? 1 : 2;   // steps in flight
+
+    const Chunk &ch;
+    SuperLds &lds;
+    const Tail &tail;
+    int N, lane;
+    int p, grp, in0;     // its half-unit: 32-sample step, group, the group's first input
+    int place;           // of the half-unit in lds.raw (even steps)
+    // operand slots: rect rows r0, r0 + 1 and columns c0, c0 + 1, triangle
+    // c0 .. c0 + 3; a rect's a, b: which of these it sums
+    int r0, c0, a, b;
+    int n;               // loop steps of the segment
+    int cur, nxt, dec;   // LDS buffers of steps s, s + 1, s + 2
+    uint32_t skip, step_bytes, cache;
+    v4i pat_re, pat_im;
+    uint32_t voff[4];
+    v4i in[kSets][kTo - kFrom];   // steps in flight
+    uint32_t r[16];           // rows being packed
+    Packer pk;
+    v6i A[4], B[4];           // triangle blocks; rect: rows A[0..1], B[0..1], columns A[2..3]
+    v16f acc[8];              // rect: re, im of tile (i, c) at 4 i + 2 c
+    v4f sum[2];               // triangle: its two diagonal blocks; rect: column a, row b
+
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows(int j) const {
+        return chunk_rsrc(ch, (uint32_t)j * step_bytes + skip);
+    }
+    // validity of the half-unit's samples in step j (ascending)
+    __device__ __forceinline__ uint32_t bits_of(int j) {
+        if ((j & 31) == 0 && j < n) cache = lds.words[2 * j + lane];
+        return j < n ? (uint32_t)__builtin_amdgcn_readlane((int)cache, 2 * (j & 31) + p) : 0u;
+    }
+    __device__ __forceinline__ uint8_t *raw(int x) const {
+        return lds.raw[place + (ROLE == kOffFull ? 0 : x * (kOff ? 2 : 4))];
+    }
+    // Step j (parity X) from registers into LDS, and step j + 2 requested.  A
+    // wave with a half-unit of its own has read its previous one; the others
+    // alternate between two places, with a barrier between writers and readers.
+    template <int X>
+    __device__ __forceinline__ void hand_over(int j) {
+        constexpr int set = X % kSets;
+        store_raw<kFrom, kTo>(raw(X), in[set], bits_of(j), 2 * j + p, tail, lds.tails, N, in0,
+                              lane);
+        load_raw<kFrom, kTo>(rows(j + kSets), voff, in[set]);
+    }
+    // Piece K of packing a step (parity X) into buffer dst; the step after
+    // (j + 1) is handed over in between.
+    template <int X, int K>
+    __device__ __forceinline__ void piece(int j, uint8_t *dst) {
+        constexpr int k = K % 8;
+        constexpr bool re = ROLE == kOffFull ? K >= 8 : kRe;
+        if constexpr (K == 1) hand_over<1 - X>(j + 1);
+        if constexpr (k < 4)
+            pk.template pack<re, k>(r);
+        else if constexpr (k < 7)
+            pk.template transpose<k - 4>();
+        else
+            pk.write(dst + 4 * grp * kSlotBytes + (re ? 0 : kCompBytes), p, lane);
+    }
+    // the pieces that follow matrix instruction M (M < 0: all)
+    template <int X, int M, int K>
+    __device__ __forceinline__ void pieces_at(int j, uint8_t *dst) {
+        if constexpr (K < kAll) {
+            if constexpr (M < 0 || kLead + K * (kSpan - kLead) / kAll == M) piece<X, K>(j, dst);
+            pieces_at<X, M, K + 1>(j, dst);
         }
     }
-}
-
-// ---------------------------------------------------------------------------
-// the tiles of one wave
-// ---------------------------------------------------------------------------
-
-// Three tile shapes (see plan.hpp), 16 MFMAs per 32-sample step each:
-//   kRect: row block s0 x column blocks c0 .. c0+3 (4 off-diagonal tiles);
-//   kTriA: of the 4 blocks s0 .. s0+3, the diagonal tiles of blocks 0 and 1
-//          (as Q) and the pairs (0,1) (0,2) (0,3);
-//   kTriB: the diagonal tiles of blocks 2 and 3 and the pairs (1,2) (1,3)
-//          (2,3).
-enum Shape { kRect = 0, kTriA = 1, kTriB = 2 };
-
-template <int SHAPE>
-struct Tiles;
-
-template <>
-struct Tiles<kRect> {
-    static constexpr int NQ = 0, NO = 4, NT = 4, NXP = 1;
-    __device__ static constexpr int qb(int) { return 0; }
-    __device__ static constexpr int row(int) { return 0; }
-    __device__ static constexpr int col(int t) { return t; }
-    __device__ static constexpr int xpi(int) { return 0; }  // Xp index of a row
-};
-
-template <>
-struct Tiles<kTriA> {
-    static constexpr int NQ = 2, NO = 3, NT = 5, NXP = 1;
-    __device__ static constexpr int qb(int k) { return k; }
-    __device__ static constexpr int row(int) { return 0; }
-    __device__ static constexpr int col(int t) { return t + 1; }
-    __device__ static constexpr int xpi(int) { return 0; }
-};
-
-template <>
-struct Tiles<kTriB> {
-    static constexpr int NQ = 2, NO = 3, NT = 5, NXP = 2;
-    __device__ static constexpr int qb(int k) { return 2 + k; }
-    __device__ static constexpr int row(int t) { return t < 2 ? 1 : 2; }
-    __device__ static constexpr int col(int t) { return t < 2 ? t + 2 : 3; }
-    __device__ static constexpr int xpi(int i) { return i - 1; }
-};
-
-template <int SHAPE>
-struct Acc {
-    using T = Tiles<SHAPE>;
-    v16i q[T::NQ > 0 ? T::NQ : 1];
-    v16i re[T::NO], im[T::NO];
-};
-
-// Operand fragments of one 16-sample sub-step.  kRect: x[0] = the row
-// block, y[j] = column block c0 + j.  kTriA/B: x[i] = block s0 + i (the
-// ones the shape uses), xs[k] = Xs of its k-th diagonal block.
-template <int SHAPE>
-struct Ops {
-    static constexpr bool kTri = SHAPE != kRect;
-    v4i x[kTri ? 4 : 1];
-    v4i y[kTri ? 1 : 4];
-    v4i xs[kTri ? 2 : 1];
-};
-
-template <int SHAPE>
-__device__ __forceinline__ void read_ops(const uint8_t *buf, int slot_bytes, int s0, int c0,
-                                         int sub, Ops<SHAPE> &o) {
-    const int lane = threadIdx.x & 63;
-    auto frag = [&](int s, int op) {
-        return *(const v4i *)(buf + chunk_off(slot_bytes, s, op, sub, lane));
-    };
-    if (SHAPE == kRect) {
-        o.x[0] = frag(s0, 0);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) o.y[j] = frag(c0 + j, 0);
-    } else {
-#pragma unroll
-        for (int i = SHAPE == kTriA ? 0 : 1; i < 4; ++i) o.x[i] = frag(s0 + i, 0);
-#pragma unroll
-        for (int k = 0; k < 2; ++k) o.xs[k] = frag(s0 + Tiles<SHAPE>::qb(k), 1);
+    __device__ __forceinline__ v6i op_at(int buf, int slot, int comp) const {
+        return read_op(lds.stage + buf + slot * kSlotBytes + comp * kCompBytes, lane);
     }
-}
-
-// One loop step: the 16 MFMAs of step s, with the decode of step s + 2
-// woven into them and the operands of the next sub-steps read ahead
-// (kMma = false: the decode only, for the rectangle waves of the halves
-// geometry, whose tiles would pair different time steps).
-//   * (s, sub 0) operands arrive in `o`, read during the previous step;
-//     (s, sub 1) operands are read at the start; (s + 1, sub 0) operands
-//     are read into `o` once the sub-0 MFMAs have taken theirs, so the next
-//     step starts its MFMAs as soon as it passes the barrier.
-//   * the decode of step s + 2 comes in small pieces (a 4x4 transpose, or
-//     the decode and LDS write of one input) between MFMAs, spread over the
-//     first 14 of them so the last LDS write lands before the barrier.  A
-//     piece's VALU work issues while the MFMA before it occupies the matrix
-//     core; scheduling barriers keep the order.
-template <int SHAPE, bool kXs, int UPT, bool kMma, bool kSmall>
-__device__ __forceinline__ void pipelined_step(const uint8_t *cur, const uint8_t *next,
-                                               uint8_t *dec, int slot_bytes, int s0, int c0,
-                                               Acc<SHAPE> &acc, const Unit (&u)[UPT],
-                                               const Prefetch<UPT> &p, uint32_t vb0,
-                                               uint32_t vb1, Ops<SHAPE> &o) {
-    // 5 pieces: the transposes of all units, then input c of all units;
-    // the units' chains are independent, so a piece has UPT-fold ILP
-    constexpr int kPieces = 5;
-    constexpr int kSpan = 14;
-    using TL = Tiles<SHAPE>;
-    Ops<SHAPE> o1;
-    if (kMma) read_ops(cur, slot_bytes, s0, c0, 1, o1);
-    // decode state
-    uint32_t L[UPT][4];
-    uint32_t msk[UPT];
-    auto piece = [&](int k) {
-        const int c = k - 1;
-        if (c < 0) {
-#pragma unroll
-            for (int r = 0; r < UPT; ++r) {
-                transpose4(p.d[r], L[r]);
-                const uint32_t vbits = kSmall && u[r].hi ? vb1 : vb0;
-                const uint32_t vq = u[r].act ? (vbits >> (4 * u[r].sq)) & 15u : 0u;
-                msk[r] = bits_to_bytes(vq);
+    // Matrix instruction M of the step, and the operand reads and input sums
+    // that follow it.  A register set is read again as soon as its last use
+    // is issued.
+    template <int M>
+    __device__ __forceinline__ void op() {
+        if constexpr (kTri) {
+            constexpr TriOp t = tri_op<kHalfB>(M);
+            constexpr bool row_a = M < 5 || (M >= 10 && M < 15);
+            acc[t.acc] = mfma(row_a ? A[t.row] : B[t.row], M < 10 ? A[t.col] : B[t.col], acc[t.acc]);
+            constexpr int s = kHalfB ? 2 : 0;   // its diagonal blocks: s, s + 1
+            if constexpr (M < 2) sum_mfma(pat_re, A[s + M], sum[M]);
+            if constexpr (M == 10 || M == 11) sum_mfma(pat_im, B[s + M - 10], sum[M - 10]);
+            if constexpr (M < (kHalfB ? 3 : 4)) B[M + (kHalfB ? 1 : 0)] =
+                op_at(cur, c0 + M + (kHalfB ? 1 : 0), 1);
+            if constexpr (!kHalfB) {
+                if constexpr (M == 5) A[0] = negate(A[0]);
+                if constexpr (M == 7) A[1] = negate(A[1]);
+                if constexpr (M == 10) A[2] = op_at(nxt, c0 + 2, 0);
+                if constexpr (M == 11) A[3] = op_at(nxt, c0 + 3, 0);
+                if constexpr (M == 14) A[0] = op_at(nxt, c0, 0);
+                if constexpr (M == 15) A[1] = op_at(nxt, c0 + 1, 0);
+            } else {
+                if constexpr (M == 4) A[1] = negate(A[1]);
+                if constexpr (M == 6) A[2] = negate(A[2]);
+                if constexpr (M == 9) A[3] = negate(A[3]);
+                if constexpr (M == 12) A[1] = op_at(nxt, c0 + 1, 0);
+                if constexpr (M == 14) A[2] = op_at(nxt, c0 + 2, 0);
+                if constexpr (M == 15) A[3] = op_at(nxt, c0 + 3, 0);
             }
         } else {
-#pragma unroll
-            for (int r = 0; r < UPT; ++r) {
-                const int oo = u[r].sq >> 1, h = u[r].sq & 1;
-                uint32_t Lm = (L[r][c] & msk[r]) | (0x88888888u & ~msk[r]);
-                uint32_t an = (Lm >> 4) & 0x0f0f0f0fu, bn = Lm & 0x0f0f0f0fu;
-                uint8_t *dst = dec + chunk_off(slot_bytes, u[r].s, 0, oo >> 1,
-                                               (oo & 1) * 32 + 4 * u[r].q + c) + 8 * h;
-                v2u xr = {nib_to_s8(an), nib_to_s8(bn)};
-                *(v2u *)dst = xr;
-                if (kXs) {
-                    v2u v = {(an + bn + 0x70707070u) ^ 0x80808080u,
-                             ((bn | 0x80808080u) - an) ^ 0x80808080u};
-                    *(v2u *)(dst + kFragBytes) = v;
+            // by column: A rows, B rows x A of column 0; B, A rows x A of
+            // column 1; then B rows, -A rows x B of column 0; -A, B x B of 1
+            constexpr int i = M & 1, ph = M / 2, c = (ph >> 1) & 1;
+            constexpr bool row_a = ph == 0 || ph == 3 || ph == 5 || ph == 6;
+            constexpr bool im = (ph < 4) != row_a;
+            constexpr int y = 4 * i + 2 * c + (im ? 1 : 0);
+            acc[y] = mfma(row_a ? A[i] : B[i], A[2 + c], acc[y]);
+            if constexpr (kOff) {
+                if constexpr (M == 1 || M == 9)
+                    if (a == 0) sum_mfma(M == 1 ? pat_re : pat_im, A[2], sum[0]);
+                if constexpr (M == 5 || M == 13)
+                    if (a == 1) sum_mfma(M == 5 ? pat_re : pat_im, A[3], sum[0]);
+                if constexpr (M == 3) {
+                    if (b == 0) {
+                        sum_mfma(pat_re, A[0], sum[1]);
+                        sum_mfma(pat_im, B[0], sum[1]);
+                    }
+                    if (b == 1) {
+                        sum_mfma(pat_re, A[1], sum[1]);
+                        sum_mfma(pat_im, B[1], sum[1]);
+                    }
                 }
             }
+            if constexpr (M == 3) A[2] = op_at(cur, c0, 1);
+            if constexpr (M == 7) A[3] = op_at(cur, c0 + 1, 1);
+            if constexpr (M == 6 || M == 7) A[M - 6] = negate(A[M - 6]);
+            if constexpr (M == 11) A[2] = op_at(nxt, c0, 0);
+            if constexpr (M == 12 || M == 13) A[M - 12] = op_at(nxt, r0 + M - 12, 0);
+            if constexpr (M == 14 || M == 15) B[M - 14] = op_at(nxt, r0 + M - 14, 1);
+            if constexpr (M == 15) A[3] = op_at(nxt, c0 + 1, 0);
         }
-    };
-    v4i xp[TL::NXP];
-    auto rows_xp = [&](const Ops<SHAPE> &q) {
-        if (SHAPE == kRect) {
-            xp[0] = make_xp(q.x[0]);
+    }
+    template <int X, int M>
+    __device__ __forceinline__ void ops(int j, uint8_t *dst) {
+        if constexpr (M < kOps) {
+            op<M>();
+            if constexpr (M == 0) read_raw(raw(X), lane, r);
+            pieces_at<X, M, 0>(j, dst);
+            __builtin_amdgcn_sched_barrier(0);
+            ops<X, M + 1>(j, dst);
+        }
+    }
+    // matrix instructions of step s (parity X), packing of step s + 2
+    template <int X>
+    __device__ __forceinline__ void step(int s) {
+        ops<X, 0>(s + 2, lds.stage + dec);
+        __syncthreads();
+        const int t = cur;
+        cur = nxt;
+        nxt = dec;
+        dec = t;
+    }
+    template <int X>
+    __device__ __forceinline__ void prologue_step() {
+        read_raw(raw(X), lane, r);
+        pieces_at<X, -1, 0>(X, lds.stage + X * kBufBytes);
+        __syncthreads();
+    }
+    // the operands that the first step expects
+    __device__ __forceinline__ void first_ops() {
+        if constexpr (kTri) {
+#pragma unroll
+            for (int c = kHalfB ? 1 : 0; c < 4; ++c) A[c] = op_at(0, c0 + c, 0);
         } else {
 #pragma unroll
-            for (int i = 0; i < TL::NXP; ++i) xp[i] = make_xp(q.x[TL::row(2 * i)]);
+            for (int i = 0; i < 2; ++i) {
+                A[i] = op_at(0, r0 + i, 0);
+                B[i] = op_at(0, r0 + i, 1);
+                A[2 + i] = op_at(0, c0 + i, 0);
+            }
         }
-    };
-    // MFMA k (0..7) of a sub-step
-    auto mfma_op = [&](const Ops<SHAPE> &q, int k) {
-        if (SHAPE == kRect) {
-            const int t = k / 2;
-            if (k % 2 == 0)
-                acc.re[t] = mfma(q.x[0], q.y[t], acc.re[t]);
-            else
-                acc.im[t] = mfma(xp[0], q.y[t], acc.im[t]);
-        } else if (k < 2) {
-            acc.q[k] = mfma(q.xs[k], q.x[TL::qb(k)], acc.q[k]);
-        } else {
-            const int t = (k - 2) / 2;
-            const int i = TL::row(t), j = TL::col(t);
-            if (k % 2 == 0)
-                acc.re[t] = mfma(q.x[i], q.x[j], acc.re[t]);
-            else
-                acc.im[t] = mfma(xp[TL::xpi(i)], q.x[j], acc.im[t]);
+    }
+    // input sums into LDS, in units of 1/8 of an input's T and D
+    __device__ __forceinline__ void put_sum(int slot, const v4f &x) {
+        v2i *d = lds.sums + slot * kBlk + lane;
+        d[0] = (v2i){units(x.x + x.z), units(x.x - x.z)};
+        d[16] = (v2i){units(x.y + x.w), units(x.y - x.w)};
+    }
+    __device__ __forceinline__ void put_sums() {
+        if (lane >= 16) return;
+        if constexpr (kTri) {
+            put_sum(c0 + (kHalfB ? 2 : 0), sum[0]);
+            put_sum(c0 + (kHalfB ? 3 : 1), sum[1]);
+        } else if constexpr (kOff) {
+            put_sum(c0 + a, sum[0]);
+            if (b < 2) put_sum(r0 + b, sum[1]);
         }
-    };
+    }
+    // accumulators of slice S of a rect: rows 8 (S % 4) .. of row block S / 4,
+    // t[4 v + 2 c + (0 re, 1 im)]
+    template <int S, int E>
+    __device__ __forceinline__ void take(float (&t)[16]) const {
+        if constexpr (E < 16) {
+            t[E] = acc[4 * (S / 4) + E % 4][4 * (S % 4) + E / 4];
+            take<S, E + 1>(t);
+        }
+    }
+    // the accumulators into a triangle's dump
+    template <int K>
+    __device__ __forceinline__ void put_dump(float *dump, int ln) const {
+        if constexpr (K < 8) {
+            put_unit<false, tri_unit<kHalfB>(K)>(dump, acc[K], ln);
+            put_dump<K + 1>(dump, ln);
+        }
+    }
+};
 
-    if (kMma) rows_xp(o);
+// The tiles of a rect wave: a lane holds 2 consecutive inputs j of a row, 16
+// bytes of the output (another wave the next two).  In a loop of 8 slices of 4
+// rows (per lane), so that the code stays small: it runs once per workgroup,
+// from a cold instruction cache, and unrolled over all accumulators of four
+// waves it took 70 us.
+template <int ROLE, bool kAdd>
+__device__ __forceinline__ void write_rect_as(const SuperWave<ROLE> &w, const v2i *sums,
+                                              int valid128, int row_in0, int col_in0, int N,
+                                              __amdgpu_buffer_rsrc_t out, int lane) {
+    const int jj = lane & 31, j0 = col_in0 + 4 * jj + (w.c0 & 3);
+    v2i sj[2];
 #pragma unroll
-    for (int m = 0; m < 16; ++m) {
-        if (kMma) {
-            if (m == 8) rows_xp(o1);
-            if (m == 9) read_ops(next, slot_bytes, s0, c0, 0, o);
-            if (m < 8)
-                mfma_op(o, m);
-            else
-                mfma_op(o1, m - 8);
+    for (int c = 0; c < 2; ++c) {
+        sj[c] = sums[(w.c0 + c) * kBlk + jj];
+        sj[c].x = valid128 - sj[c].x;
+    }
+    // row v of slice s, from element c on
+    auto offset = [&](int s, int v, int c) -> uint32_t {
+        const int i = row_in0 + 4 * (8 * (s & 3) + 4 * (lane >> 5) + v) + ((w.r0 + (s >> 2)) & 3);
+        const uint32_t at = tri_bytes(N, i, j0 + c);
+        return i < N && j0 + c < N ? at : kNowhere;
+    };
+    const bool pairs = N % 2 == 0;   // uniform: whole pairs, else element by element
+    v4i old[4];
+    auto load_old = [&](int s) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (pairs) {
+                old[v] = __builtin_amdgcn_raw_buffer_load_b128(out, (int)offset(s, v, 0), 0, 0);
+            } else {
+                const v2i y = __builtin_amdgcn_raw_buffer_load_b64(out, (int)offset(s, v, 0), 0, 0);
+                const v2i z = __builtin_amdgcn_raw_buffer_load_b64(out, (int)offset(s, v, 1), 0, 0);
+                old[v] = (v4i){y.x, y.y, z.x, z.y};
+            }
         }
+    };
+    if (kAdd) load_old(0);
+#pragma clang loop unroll(disable)
+    for (int s = 0; s < 8; ++s) {
+        float t[16];
+        switch (s) {
+            case 0: w.template take<0, 0>(t); break;
+            case 1: w.template take<1, 0>(t); break;
+            case 2: w.template take<2, 0>(t); break;
+            case 3: w.template take<3, 0>(t); break;
+            case 4: w.template take<4, 0>(t); break;
+            case 5: w.template take<5, 0>(t); break;
+            case 6: w.template take<6, 0>(t); break;
+            default: w.template take<7, 0>(t); break;
+        }
+        v4i x[4];
 #pragma unroll
-        for (int q = 0; q < kPieces; ++q)
-            if (q * kSpan / kPieces == m) piece(q);
-        __builtin_amdgcn_sched_barrier(0);
+        for (int v = 0; v < 4; ++v) {
+            const v2i si = sums[(w.r0 + (s >> 2)) * kBlk + 8 * (s & 3) + 4 * (lane >> 5) + v];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                x[v][2 * c] = units(t[4 * v + 2 * c]) + sj[c].x - si.x;
+                x[v][2 * c + 1] = units(t[4 * v + 2 * c + 1]) - sj[c].y + si.y;
+            }
+            if (kAdd) x[v] += old[v];
+        }
+        if (kAdd && s < 7) load_old(s + 1);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            if (pairs) {
+                __builtin_amdgcn_raw_buffer_store_b128(x[v], out, (int)offset(s, v, 0), 0, 0);
+            } else {
+                __builtin_amdgcn_raw_buffer_store_b64(x[v].xy, out, (int)offset(s, v, 0), 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b64(x[v].zw, out, (int)offset(s, v, 1), 0, 0);
+            }
+        }
     }
 }
 
-// Where the tiles of a wave lie: tile k < NQ is the diagonal tile of block
-// qb(k), the others pair a row block with a column block.  Element v of a
-// tile held by `lane` is (i, j) = (8 (v/4) + 4 (lane/32) + v%4, lane%32)
-// within the tile (the output layout of v_mfma_i32_32x32x32_i8).
-template <int SHAPE>
-struct TileMap {
-    Group g;
-    int s0, c0, N;
-    __device__ void rc(int k, int &rs, int &cs) const {
-        using TL = Tiles<SHAPE>;
-        if (k < TL::NQ) {
-            rs = cs = s0 + TL::qb(k);
-        } else if (SHAPE == kRect) {
-            rs = s0;
-            cs = c0 + TL::col(k - TL::NQ);
-        } else {
-            rs = s0 + TL::row(k - TL::NQ);
-            cs = s0 + TL::col(k - TL::NQ);
+template <int ROLE>
+__device__ __forceinline__ void write_rect(const SuperWave<ROLE> &w, const v2i *sums, int valid128,
+                                           int row_in0, int col_in0, int N, const Dest &d,
+                                           int lane) {
+    if (d.add)
+        write_rect_as<ROLE, true>(w, sums, valid128, row_in0, col_in0, N, d.rsrc, lane);
+    else
+        write_rect_as<ROLE, false>(w, sums, valid128, row_in0, col_in0, N, d.rsrc, lane);
+}
+
+template <int ROLE>
+__device__ __forceinline__ void run_super(const CorrArgs &a, const Group &g, int f, int gid,
+                                          int split, int wave, SuperLds &lds) {
+    using W = SuperWave<ROLE>;
+    const int t_begin = split * a.steps_per_split * kStep;
+    int t_end = t_begin + a.steps_per_split * kStep;
+    if (t_end > a.T) t_end = a.T;
+    const int loops = (t_end - t_begin + kLoop - 1) / kLoop;
+    const int segs = (loops + kSegSteps - 1) / kSegSteps;
+    const int per = (loops + segs - 1) / segs;
+    int counted = 0;
+
+    for (int seg = 0; seg < segs; ++seg) {
+        const int t_seg = t_begin + seg * per * kLoop;
+        const int t_stop = t_seg + per * kLoop < t_end ? t_seg + per * kLoop : t_end;
+        const Chunk ch = make_chunk(a, f, t_seg, t_stop);
+        const Tail tail = make_tail(a, f, t_seg, lds.tails);
+        W w = {ch, lds, tail};
+        w.N = a.N;
+        w.lane = threadIdx.x & 63;
+        w.p = (wave >> 1) & 1;
+        w.grp = !W::kOff ? wave & 1 : ROLE == kOffFull ? 1 + (wave & 1) : 0;
+        w.in0 = group_input(g, w.grp);
+        w.place = !W::kOff ? wave & 3 : ROLE == kOffFull ? wave : 4 + w.p;
+        w.a = wave & 1;
+        w.b = wave >> 1;
+        w.r0 = 2 * w.a;
+        w.c0 = W::kTri ? 4 * (wave >> 1 & 1) : 4 + 2 * w.b;
+        w.n = (t_stop - t_seg + kLoop - 1) / kLoop;
+        w.step_bytes = kLoop * ch.row;
+        w.skip = 32u * (uint32_t)w.p * ch.row + (uint32_t)w.in0;
+        w.cache = 0;
+        w.pat_re = sum_pattern(false, w.lane);
+        w.pat_im = sum_pattern(true, w.lane);
+        raw_offsets(w.voff, ch.row, w.lane);
+        load_raw<W::kFrom, W::kTo>(w.rows(0), w.voff, w.in[0]);
+        if constexpr (W::kSets == 2) load_raw<W::kFrom, W::kTo>(w.rows(1), w.voff, w.in[1]);
+        if (threadIdx.x == 0) lds.valid = 0;
+        const int my_valid = fill_words<kSuperThreads>(a, f, t_seg, t_stop, 2 * w.n, lds.words);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w.acc[k] = (v16f){0};
+#pragma unroll
+        for (int k = 0; k < 2; ++k) w.sum[k] = (v4f){0};
+        __syncthreads();
+        w.template hand_over<0>(0);
+        __syncthreads();
+        w.template prologue_step<0>();
+        w.template prologue_step<1>();
+        w.cur = 0;
+        w.nxt = kBufBytes;
+        w.dec = 2 * kBufBytes;
+        w.first_ops();
+        // pairs of steps (two register sets in flight); a step past the
+        // segment's last adds zeros
+        for (int s = 0; s < w.n; s += 2) {
+            w.template step<0>(s);
+            w.template step<1>(s + 1);
+        }
+
+        // ---- sums out -----------------------------------------------------
+        const int lane = keep_late(threadIdx.x & 63);
+        atomicAdd(&lds.valid, my_valid);
+        if constexpr (W::kTri) w.template put_dump<0>(lds.dump[w.c0 >> 2], lane);
+        w.put_sums();
+        __syncthreads();
+        const int valid = lds.valid;
+        counted += valid;
+        const Dest d = make_dest(a, f, split, seg == 0);
+        if constexpr (!W::kTri)
+            write_rect(w, lds.sums, 128 * valid, group_input(g, 0), group_input(g, w.c0 >> 2), a.N,
+                       d, lane);
+        // The triangles' 32 row quads each: 6 per triangle wave, 2 (of the
+        // short rows) per rect wave, which has its own tiles to write.
+        if constexpr (!W::kOff) {
+            const int q0 = W::kTri ? wave - 4 : 24 + 2 * wave;
+            const int q1 = W::kTri ? 24 : q0 + 2;
+#pragma clang loop unroll(disable)
+            for (int k = 0; k < 2; ++k)
+                write_triangle<W::kTri ? 6 : 2>(lds.dump[k], lds.sums + 4 * k * kBlk, 128 * valid,
+                                                group_input(g, k), a.N, d, q0, q1,
+                                                W::kTri ? 4 : 1, lane);
+        }
+        if (seg + 1 < segs) __syncthreads();   // the dump and sums are free
+    }
+    if (a.count && gid == 0 && threadIdx.x == 0)
+        a.count[f] = a.overwrite ? counted : a.count[f] + counted;
+}
+
+// ---------------------------------------------------------------------------
+// halves geometry
+// ---------------------------------------------------------------------------
+
+// A whole triangle: Q[c] = acc[c], pair t (01 02 03 12 13 23) re = acc[4 + 2 t],
+// im = the next.
+__device__ constexpr int pair_lo(int t) { return t < 3 ? 0 : t < 5 ? 1 : 2; }
+__device__ constexpr int pair_hi(int t) { return t < 3 ? t + 1 : t < 5 ? t - 1 : 3; }
+constexpr int kTriOps = 40;
+
+// Matrix instruction m of a triangle's loop step on the components A, B of
+// its four blocks.  0..9: A against A; 10..19: B rows against A columns,
+// column block by column block, so that block c of A may be negated once
+// its column is done (m == neg_after(c)); 20..29: -A rows against B; 30..39:
+// B against B.
+__device__ constexpr int tri_tile(int k) {   // k = 0..9 by column block: Q0 | 01 Q1 | 02 12 Q2 | ...
+    return k == 0 ? 0 : k == 1 ? 4 : k == 2 ? 1 : k == 3 ? 5 : k == 4 ? 7 : k == 5 ? 2
+         : k == 6 ? 6 : k == 7 ? 8 : k == 8 ? 9 : 3;
+}
+__device__ constexpr int tri_row_block(int tile) { return tile < 4 ? tile : pair_lo(tile - 4); }
+__device__ constexpr int tri_col_block(int tile) { return tile < 4 ? tile : pair_hi(tile - 4); }
+// by row block: Q0 01 02 03 | Q1 12 13 | ...
+__device__ constexpr int tri_tile_rows(int k) {
+    return k == 0 ? 0 : k < 4 ? k + 3 : k == 4 ? 1 : k < 7 ? k + 2 : k == 7 ? 2 : k == 8 ? 9 : 3;
+}
+
+template <int M>
+__device__ __forceinline__ void tri_mfma(const v6i (&A)[4], const v6i (&B)[4], v16f (&acc)[16]) {
+    constexpr int k = M % 10, ph = M / 10;
+    constexpr int tile = ph == 2 ? tri_tile_rows(k) : tri_tile(k);
+    constexpr int r = tri_row_block(tile), c = tri_col_block(tile);
+    constexpr bool im = ph == 1 || ph == 2;
+    constexpr int x = tile < 4 ? tile : 4 + 2 * (tile - 4) + (im ? 1 : 0);
+    acc[x] = mfma(ph == 0 || ph == 2 ? A[r] : B[r], ph < 2 ? A[c] : B[c], acc[x]);
+}
+// the matrix instruction after which block c of A is free as a column
+template <int M>
+__device__ __forceinline__ void tri_negate(v6i (&A)[4]) {
+    if constexpr (M == 10) A[0] = negate(A[0]);
+    if constexpr (M == 12) A[1] = negate(A[1]);
+    if constexpr (M == 15) A[2] = negate(A[2]);
+    if constexpr (M == 19) A[3] = negate(A[3]);
+}
+
+struct SmallLds {
+    union {
+        uint8_t raw[kSmallWaves][2][kRawBytes];   // a wave's next loop step
+        float dump[2][kDump];
+    };
+    uint32_t words[2 * kSegSteps];
+    int sums[4 * kBlk * 2];
+    uint32_t tails[kMaxCut];
+    int valid;
+};
+
+struct SmallWave {
+    static constexpr int kAll = 32;   // pieces of packing per step
+    const Chunk &ch;
+    SmallLds &lds;
+    const Tail &tail;
+    int N, lane, in0, n;
+    v4i pat_re, pat_im;
+    int wave;
+    uint32_t voff[4];
+    v4i in[2][2][4];      // steps in flight: [set][32-sample step]
+    uint32_t r[16];       // rows being packed
+    uint32_t cache;
+    Packer pk;
+    v6i A[2][4], B[2][4];
+    v16f acc[16];
+    v4f sum[4];
+
+    // 32-sample step P of step j
+    __device__ __forceinline__ __amdgpu_buffer_rsrc_t rows(int j, int P) const {
+        return chunk_rsrc(ch, (uint32_t)(2 * j + P) * 32 * ch.row + (uint32_t)in0);
+    }
+    // Validity of 32-sample step P of step j = wave + 4 i (ascending): a lane
+    // keeps the words of the next 32 steps of the wave.
+    template <int P>
+    __device__ __forceinline__ uint32_t bits_of(int j) {
+        const int i = (j - wave) >> 2;
+        if (P == 0 && (i & 31) == 0 && j < n) {
+            const int w = 2 * (j + 4 * (lane >> 1)) + (lane & 1);
+            cache = lds.words[w < 2 * n ? w : 0];
+        }
+        return j < n ? (uint32_t)__builtin_amdgcn_readlane((int)cache, 2 * (i & 31) + P) : 0u;
+    }
+    // 32-sample step P of step j (set X) from registers into LDS, and of step
+    // j + 8 requested
+    template <int X, int P>
+    __device__ __forceinline__ void hand_over(int j) {
+        const uint32_t bits = bits_of<P>(j);
+        store_raw<0, 4>(lds.raw[wave][P], in[X][P], bits, 2 * j + P, tail, lds.tails, N, in0,
+                        lane);
+        load_raw<0, 4>(rows(j + 8, P), voff, in[X][P]);
+    }
+    // Piece K of packing step j (set X) into operands An, Bn, handing over
+    // step j + 4
+    template <int X, int K>
+    __device__ __forceinline__ void piece(int j, v6i (&An)[4], v6i (&Bn)[4]) {
+        constexpr int P = K / 16, k = K % 8;
+        constexpr bool re = K / 8 % 2 == 1;
+        if constexpr (K == 1 || K == 17) hand_over<1 - X, P>(j + 4);
+        if constexpr (K == 12) read_raw(lds.raw[wave][1], lane, r);
+        if constexpr (k < 4)
+            pk.template pack<re, k>(r);
+        else if constexpr (k < 7)
+            pk.template transpose<k - 4>();
+        else
+            pk.template keep<P, 0>(re ? An : Bn);
+    }
+    // the pieces that follow matrix instruction M (M < 0: all)
+    template <int X, int M, int K>
+    __device__ __forceinline__ void pieces_at(int j, v6i (&An)[4], v6i (&Bn)[4]) {
+        if constexpr (K < kAll) {
+            if constexpr (M < 0 || 4 + K * (kTriOps - 4) / kAll == M) piece<X, K>(j, An, Bn);
+            pieces_at<X, M, K + 1>(j, An, Bn);
         }
     }
-    // index of the element in the packed triangle, or -1 when it lies below
-    // the diagonal or past N
-    __device__ int64_t elem(int k, int v, int lane) const {
-        int rs, cs;
-        rc(k, rs, cs);
-        const int i = slot_block(g, rs) * kBlk + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        const int j = slot_block(g, cs) * kBlk + (lane & 31);
-        if (i > j || j >= N) return -1;
-        return (int64_t)i * N - (int64_t)i * (i - 1) / 2 + (j - i);
+    template <int X, int M>
+    __device__ __forceinline__ void ops(int j, v6i (&Ac)[4], v6i (&Bc)[4], v6i (&An)[4],
+                                        v6i (&Bn)[4]) {
+        if constexpr (M < kTriOps) {
+            tri_mfma<M>(Ac, Bc, acc);
+            if constexpr (M < 4) sum_mfma(pat_re, Ac[M], sum[M]);
+            if constexpr (M >= 10 && M < 14) sum_mfma(pat_im, Bc[M - 10], sum[M - 10]);
+            tri_negate<M>(Ac);
+            if constexpr (M == 0) read_raw(lds.raw[wave][0], lane, r);
+            pieces_at<X, M, 0>(j, An, Bn);
+            __builtin_amdgcn_sched_barrier(0);
+            ops<X, M + 1>(j, Ac, Bc, An, Bn);
+        }
+    }
+    // step j from the operands of set K; the wave's next is packed into the
+    // other
+    template <int K>
+    __device__ __forceinline__ void step(int j) {
+        ops<1 - K, 0>(j + 4, A[K], B[K], A[1 - K], B[1 - K]);
     }
 };
 
-// The role of wave `wave` in a tile group: its staging share, tile shape and
-// first row / column slot.  Waves w and w + 4 share a SIMD: each SIMD gets
-// one rectangle and (diagonal group) one half triangle.
-template <int NSLOT_, int SHAPE_, int UPT_, bool kMma_ = true, bool kSmall_ = false>
-struct Role {
-    static constexpr int NSLOT = NSLOT_, SHAPE = SHAPE_, UPT = UPT_;
-    static constexpr bool kMma = kMma_;     // runs MFMAs (else stages only)
-    static constexpr bool kSmall = kSmall_;  // the halves geometry
-};
+// Wave w takes loop steps w, w + 4, ... of the chunk.
+__device__ __forceinline__ void run_small(const CorrArgs &a, const Group &g, int f, int split,
+                                          int wave, SmallLds &lds) {
+    const int t_begin = split * a.steps_per_split * kStep;
+    int t_end = t_begin + a.steps_per_split * kStep;
+    if (t_end > a.T) t_end = a.T;
+    const int loops = (t_end - t_begin + kLoop - 1) / kLoop;
+    const int segs = (loops + kSegSteps - 1) / kSegSteps;
+    const int per = (loops + segs - 1) / segs;
+    int counted = 0;
 
-// Which role sets a caller instantiates: kAllKinds (decides per group), or
-// only the groups of one geometry (the two persistent batch kernels, so
-// that each is register-allocated for its own roles).
-enum Kinds { kAllKinds = 0, kSuperOnly = 1, kHalvesOnly = 2 };
+    for (int seg = 0; seg < segs; ++seg) {
+        const int t_seg = t_begin + seg * per * kLoop;
+        const int t_stop = t_seg + per * kLoop < t_end ? t_seg + per * kLoop : t_end;
+        const Chunk ch = make_chunk(a, f, t_seg, t_stop);
+        const Tail tail = make_tail(a, f, t_seg, lds.tails);
+        SmallWave w = {ch, lds, tail};
+        w.N = a.N;
+        w.lane = threadIdx.x & 63;
+        w.in0 = group_input(g, 0);
+        w.n = (t_stop - t_seg + kLoop - 1) / kLoop;
+        w.pat_re = sum_pattern(false, w.lane);
+        w.pat_im = sum_pattern(true, w.lane);
+        w.wave = wave;
+        raw_offsets(w.voff, ch.row, w.lane);
+        // lanes whose inputs lie past N read nothing
+        if (w.in0 + 16 * (w.lane & 7) >= a.N)
+            for (int k = 0; k < 4; ++k) w.voff[k] = kNowhere;
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+#pragma unroll
+            for (int P = 0; P < 2; ++P) load_raw<0, 4>(w.rows(wave + 4 * k, P), w.voff, w.in[k][P]);
+        if (threadIdx.x == 0) lds.valid = 0;
+        for (int e = threadIdx.x; e < 4 * kBlk * 2; e += kSmallThreads) lds.sums[e] = 0;
+        const int my_valid = fill_words<kSmallThreads>(a, f, t_seg, t_stop, 2 * w.n, lds.words);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) w.acc[k] = (v16f){0};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) w.sum[k] = (v4f){0};
+        __syncthreads();
+        w.hand_over<0, 0>(wave);
+        w.hand_over<0, 1>(wave);
+        read_raw(lds.raw[wave][0], w.lane, w.r);
+        w.pieces_at<0, -1, 0>(wave, w.A[0], w.B[0]);
+        // pairs of steps; a step past the segment's last adds zeros
+        for (int j = wave; j < w.n; j += 8) {
+            w.step<0>(j);
+            w.step<1>(j + 4);
+        }
 
-template <int KINDS = kAllKinds, class Fn>
-__device__ __forceinline__ void with_role(const Group &g, int wave, Fn &&fn) {
-    if (KINDS == kHalvesOnly || (KINDS == kAllKinds && g.diag && g.small)) {
-        // halves geometry: the rectangle waves stage only; waves 4, 5 take
-        // the triangle of slots 0..3 (even steps), waves 6, 7 of 4..7 (odd)
-        if (wave < 4)
-            fn(Role<8, kRect, 1, false, true>{}, wave, 4);
-        else if ((wave & 1) == 0)
-            fn(Role<8, kTriA, 1, true, true>{}, 2 * (wave - 4), 0);
-        else
-            fn(Role<8, kTriB, 1, true, true>{}, 2 * (wave - 5), 0);
+        // ---- the waves' sums, added in LDS: 0 and 1 store theirs, 2 and 3 add
+        // to these, and all add the two (exact: the bound of kSegSteps covers
+        // the four of them) ----------------------------------------------------
+        const int lane = keep_late(threadIdx.x & 63);
+        __syncthreads();
+        if (wave < 2) put_triangle<false, 0>(lds.dump[wave], w.acc, lane);
+        __syncthreads();
+        if (wave >= 2) put_triangle<true, 0>(lds.dump[wave - 2], w.acc, lane);
+        atomicAdd(&lds.valid, my_valid);
+        if (lane < 16) {
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                int *s = lds.sums + 2 * (c * kBlk + lane);
+                atomicAdd(s, units(w.sum[c].x + w.sum[c].z));
+                atomicAdd(s + 1, units(w.sum[c].x - w.sum[c].z));
+                atomicAdd(s + 32, units(w.sum[c].y + w.sum[c].w));
+                atomicAdd(s + 33, units(w.sum[c].y - w.sum[c].w));
+            }
+        }
+        __syncthreads();
+        for (int e = threadIdx.x; e < kDump / 4; e += kSmallThreads)
+            ((v4f *)lds.dump[0])[e] += ((const v4f *)lds.dump[1])[e];
+        __syncthreads();
+        const int valid = lds.valid;
+        counted += valid;
+        write_triangle<4>(lds.dump[0], (const v2i *)lds.sums, 128 * valid, w.in0, a.N,
+                       make_dest(a, f, split, seg == 0), wave, kBlk, kSmallWaves, lane);
+        if (seg + 1 < segs) __syncthreads();
+    }
+    if (a.count && threadIdx.x == 0)
+        a.count[f] = a.overwrite ? counted : a.count[f] + counted;
+}
+
+// ---------------------------------------------------------------------------
+// launches
+// ---------------------------------------------------------------------------
+
+// Workgroup b runs on XCD b % 8 (round-robin dispatch); number the work so
+// that consecutive work items (the time chunks and groups of one channel)
+// share an XCD and its L2.
+__device__ __forceinline__ int64_t xcd_local_index(int64_t b, int64_t total) {
+    const int64_t per = total / 8, rem = total % 8;
+    const int64_t x = b % 8, idx = b / 8;
+    return x * per + (x < rem ? x : rem) + idx;
+}
+
+// the two kernels of one geometry each, so that each is register-allocated
+// for its own roles
+template <bool kSmall>
+using Lds = typename std::conditional<kSmall, SmallLds, SuperLds>::type;
+
+// One work item: tile group gid of channel f over time chunk `split`.
+// Every wave of a super group runs the same number of barriers; the tile
+// pattern is fixed per group kind.
+template <bool kSmall>
+__device__ __forceinline__ void run_item(const CorrArgs &a, int f, int gid, int split,
+                                         Lds<kSmall> &lds) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const Group g = make_group(a.nb, gid);
+    if constexpr (kSmall) {
+        run_small(a, g, f, split, wave, lds);
     } else if (g.diag) {
-        if (wave < 4)  // row block `wave` x columns 4..7
-            fn(Role<8, kRect, 1>{}, wave, 4);
-        else if ((wave & 1) == 0)  // triangle of blocks 0..3 (wave 4) or 4..7 (wave 6)
-            fn(Role<8, kTriA, 1>{}, 2 * (wave - 4), 0);
-        else
-            fn(Role<8, kTriB, 1>{}, 2 * (wave - 5), 0);
-    } else {
-        // row slot wave % 4 x column slots 4 + 4 (wave / 4) .. + 3
         if (wave < 4)
-            fn(Role<12, kRect, 2>{}, wave, 4);
+            run_super<kDiagRect>(a, g, f, gid, split, wave, lds);
+        else if ((wave & 1) == 0)
+            run_super<kTriA>(a, g, f, gid, split, wave, lds);
         else
-            fn(Role<12, kRect, 1>{}, wave - 4, 8);
+            run_super<kTriB>(a, g, f, gid, split, wave, lds);
+    } else {
+        if (wave < 4)
+            run_super<kOffFull>(a, g, f, gid, split, wave, lds);
+        else if ((wave & 1) == 0)
+            run_super<kOffRe>(a, g, f, gid, split, wave, lds);
+        else
+            run_super<kOffIm>(a, g, f, gid, split, wave, lds);
     }
 }
 
-// (Re, Im) partial tiles of chunk `split` (>= 1) of tile group `key`, wave
-// `wave`: [tile k][re 0..3 | im 4..7][lane] x 4 int32
-template <class T>
-__device__ __forceinline__ T *partial_tiles(T *partials, int64_t key, int splits, int split,
-                                            int wave) {
-    return partials + (key * (splits - 1) + (split - 1)) * kGroupPartial +
-           (int64_t)wave * kWavePartial;
+// One frame: workgroup -> (channel, group, chunk), groups of a channel
+// and chunks of a (channel, group) numbered next to each other.
+template <bool kSmall>
+__global__ __launch_bounds__(kSmall ? kSmallThreads : kSuperThreads, kSmall ? 1 : 2) void corr_kernel(CorrArgs a) {
+    __shared__ __attribute__((aligned(16))) Lds<kSmall> lds;
+    const int G = a.groups;
+    const int64_t total = (int64_t)a.F * G * a.splits;
+    int64_t w = xcd_local_index(blockIdx.x, total);
+    const int gid = (int)(w % G);
+    w /= G;
+    const int split = (int)(w % a.splits);
+    const int f = (int)(w / a.splits);
+    run_item<kSmall>(a, f, gid, split, lds);
 }
+
+// ---------------------------------------------------------------------------
+// batched persistent launch
+// ---------------------------------------------------------------------------
+
+// One correlator instance of a batch, as the kernel sees it.
+struct BatchInstance {
+    const uint8_t *packed;
+    const uint8_t *mask;
+    int32_t *vis;
+    int64_t *count;
+    int32_t N, F, T, B;
+    int32_t nblk_mask, nb, groups, splits;
+    int32_t steps_per_split, pad_;
+    int64_t partial_base;    // first int32 of its chunk copies
+    int64_t partial_stride;  // int32s per chunk copy
+};
+
+struct BatchItem {
+    int32_t inst, f, gid, split;
+};
+
+// A grid of one workgroup per CU pulls work items from a queue until it is
+// empty (every workgroup reaches the exit).  The last workgroup to finish
+// resets the queue, so the next launch of the same plan starts clean and
+// the launch can be replayed from a graph.  Items are accumulated into their
+// instances' resident sums.  A batch has one list of items per geometry,
+// each drained by its own launch of this kernel.
+template <bool kSmall>
+__global__ __launch_bounds__(kSmall ? kSmallThreads : kSuperThreads, kSmall ? 1 : 2) void batch_kernel(const BatchInstance *inst,
+                                                            const BatchItem *items, int n_items,
+                                                            int *queue,
+                                                            int32_t *partials) {
+    __shared__ __attribute__((aligned(16))) Lds<kSmall> lds;
+    __shared__ int s_item;
+    for (;;) {
+        __syncthreads();  // the previous item has released LDS
+        if (threadIdx.x == 0) s_item = atomicAdd(&queue[0], 1);
+        __syncthreads();
+        const int it = __builtin_amdgcn_readfirstlane(s_item);  // uniform: scalar loads below
+        if (it >= n_items) break;
+        // every field is wave-uniform: readfirstlane keeps them in scalar
+        // registers (buffer resources and offsets must live there)
+        auto u32 = [](int32_t v) { return (int32_t)__builtin_amdgcn_readfirstlane(v); };
+        auto u64 = [](int64_t v) {
+            uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+            uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+            return (int64_t)(((uint64_t)hi << 32) | lo);
+        };
+        auto ptr = [&](const void *p) { return (void *)(uintptr_t)u64((int64_t)(uintptr_t)p); };
+        const BatchItem w = items[it];
+        const int wi = u32(w.inst), wf = u32(w.f), wg = u32(w.gid), ws = u32(w.split);
+        const BatchInstance &bi = inst[wi];
+        CorrArgs a;
+        a.packed = (const uint8_t *)ptr(bi.packed);
+        a.mask = (const uint8_t *)ptr(bi.mask);
+        a.vis = (int32_t *)ptr(bi.vis);
+        a.count = nullptr;   // count_list_kernel
+        a.partials = partials + u64(bi.partial_base);
+        a.partial_stride = u64(bi.partial_stride);
+        a.N = u32(bi.N);
+        a.F = u32(bi.F);
+        a.T = u32(bi.T);
+        a.B = u32(bi.B);
+        a.nblk_mask = u32(bi.nblk_mask);
+        a.nb = u32(bi.nb);
+        a.groups = u32(bi.groups);
+        a.splits = u32(bi.splits);
+        a.steps_per_split = u32(bi.steps_per_split);
+        a.overwrite = 0;
+        run_item<kSmall>(a, wf, wg, ws, lds);
+    }
+    if (threadIdx.x == 0) {
+        int done = atomicAdd(&queue[1], 1);
+        if (done == (int)gridDim.x - 1) {
+            queue[0] = 0;
+            queue[1] = 0;
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// merge of time chunks, valid-sample counts
+// ---------------------------------------------------------------------------
 
 // Valid samples of one channel (mask row m of nblk blocks of B samples, T
 // samples), counted by one wave: lane l takes blocks l, l + 64, ..., four
@@ -578,445 +1432,66 @@ __device__ inline int64_t valid_count(const uint8_t *m, int nblk, int B, int T, 
     return n;
 }
 
-// Q of a diagonal tile -> (Re, Im) = ((Q + Q^T) / 2, (Q - Q^T) / 2), exact
-// (Q + Q^T = 2 Re is even; int64 so the sum cannot wrap).  The transpose
-// goes through LDS (32 x 33 int32 per wave, padded against bank conflicts).
-__device__ __forceinline__ void split_q(const v16i &q, int32_t *tbuf, v16i &re, v16i &im) {
-    const int lane = threadIdx.x & 63;
-    const int col = lane & 31;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        tbuf[row * 33 + col] = q[v];
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave's LDS writes landed
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        int row = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        int64_t qij = q[v], qji = tbuf[col * 33 + row];
-        re[v] = (int32_t)((qij + qji) >> 1);
-        im[v] = (int32_t)((qij - qji) >> 1);
-    }
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    __builtin_amdgcn_wave_barrier();
-}
-
-// UPT = staging units per lane and step (wave-rounds of 64 units): the
-// 16 (diagonal) or 24 (off-diagonal) wave-rounds of a step are dealt to the
-// 8 waves as x = r * 8 + wave.
-template <bool kAligned, bool kOverwrite, int NSLOT, int SHAPE, int UPT, bool kMma, bool kSmall>
-__device__ __forceinline__ void run_wave(const CorrArgs &a, const Group &g, int f, int gid,
-                                         int split, int s0, int c0, uint8_t *lds,
-                                         uint32_t *mwords) {
-    using TL = Tiles<SHAPE>;
-    constexpr bool kDiagGroup = NSLOT == 8;
-    constexpr int SLOT = kDiagGroup ? 2 * kFragBytes : kFragBytes;
-    const int wave = threadIdx.x >> 6;
-    const int lane = threadIdx.x & 63;
-
-    const int t_begin = split * a.steps_per_split * kStep;
-    int t_end = t_begin + a.steps_per_split * kStep;
-    if (t_end > a.T) t_end = a.T;
-    // 32-sample steps of the chunk, and loop steps: one 32-sample step, or
-    // a pair of them in the halves geometry
-    const int nsteps32 = (t_end - t_begin + kStep - 1) / kStep;
-    constexpr int pair = kSmall ? 2 : 1;
-    const int nsteps = (nsteps32 + pair - 1) / pair;
-    constexpr int step_samples = pair * kStep;
-
-    const Chunk ch = make_chunk(a, f, t_begin, t_end);
-    Unit u[UPT];
-#pragma unroll
-    for (int r = 0; r < UPT; ++r) {
-        const int x = r * kWaves + wave;  // wave-round: 64 units
-        const int o = x / (NSLOT / 4), sg = x % (NSLOT / 4);
-        const int h = (lane >> 4) & 1;
-        u[r].q = lane & 7;
-        u[r].s = 4 * sg + ((lane >> 3) & 1) + 2 * ((lane >> 5) & 1);
-        u[r].sq = 2 * o + h;
-        int n0 = slot_block(g, u[r].s) * kBlk + 4 * u[r].q;
-        u[r].act = n0 < a.N;
-        u[r].hi = kSmall && u[r].s >= 4;
-        u[r].voff = u[r].act ? (uint32_t)(4 * u[r].sq + (u[r].hi ? kStep : 0)) * ch.row_bytes +
-                                   (uint32_t)n0
-                             : 0x80000000u;
-        u[r].inb = 0;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) u[r].inb |= (n0 + c < a.N ? 1u : 0u) << c;
-    }
-
-    Acc<SHAPE> acc;
-#pragma unroll
-    for (int k = 0; k < TL::NO; ++k) {
-        acc.re[k] = (v16i){0};
-        acc.im[k] = (v16i){0};
-    }
-#pragma unroll
-    for (int k = 0; k < TL::NQ; ++k) acc.q[k] = (v16i){0};
-
-    // pipeline, per step s:
-    //   raw bytes   loaded kDepth steps ahead into a ring of register sets
-    //               (set k holds steps = k mod D), loop unrolled D times so
-    //               each set has fixed registers;
-    //   decode      two steps ahead, into the third of three LDS buffers;
-    //   MFMA        from the buffer of step s, operands read ahead.
-    // Steps past the chunk are staged as zeros (the last ring is padded).
-    constexpr int D = kAligned ? kDepth : 3;
-    static_assert(D >= 3, "the ring must hold the step being decoded and two in flight");
-    // validity words: a window of kMaskWindow steps in LDS; each lane caches
-    // the word of one of the next 64 steps, read out with readlane
-    // (in 32-sample steps: loop step j uses word j, or words 2j and 2j + 1)
-    fill_mask_window(a, f, ch, 0, nsteps32, mwords);
-    Prefetch<UPT> pf[D];
-#pragma unroll
-    for (int k = 0; k < D; ++k) issue_loads<kAligned>(ch, t_begin + k * step_samples, u, pf[k]);
-    __syncthreads();
-    uint32_t mcache = mwords[lane];
-    auto vbits_of = [&](int j32) -> uint32_t {
-        return j32 < nsteps32 ? (uint32_t)__builtin_amdgcn_readlane((int)mcache, j32 & 63) : 0u;
-    };
-    commit<kDiagGroup, kSmall>(u, pf[0], vbits_of(0), vbits_of(pair - 1), lds, SLOT);
-    commit<kDiagGroup, kSmall>(u, pf[1], vbits_of(pair), vbits_of(2 * pair - 1),
-                               lds + kBufBytes, SLOT);
-    __syncthreads();
-    Ops<SHAPE> ops;
-    if (kMma) read_ops(lds, SLOT, s0, c0, 0, ops);
-    int b_cur = 0, b_next = kBufBytes, b_dec = 2 * kBufBytes;  // LDS byte offsets
-    const int npad = (nsteps + D - 1) / D * D;
-    for (int sb = 0; sb < npad; sb += D) {
-#pragma unroll
-        for (int k = 0; k < D; ++k) {
-            const int s = sb + k;
-            const int j = s + 2;   // step decoded now
-            const int j32 = pair * j;
-            if ((j32 & 63) == 0 && j32 < nsteps32) {
-                if (j32 % kMaskWindow == 0) {
-                    // next window of validity words (uniform branch, rare)
-                    fill_mask_window(a, f, ch, j32, nsteps32, mwords);
-                    __syncthreads();
-                }
-                mcache = mwords[(j32 % kMaskWindow) + lane];
-            }
-            const uint32_t vb0 = vbits_of(j32), vb1 = kSmall ? vbits_of(j32 + 1) : vb0;
-            issue_loads<kAligned>(ch, t_begin + (s + D) * step_samples, u, pf[k]);
-            pipelined_step<SHAPE, kDiagGroup, UPT, kMma, kSmall>(
-                lds + b_cur, lds + b_next, lds + b_dec, SLOT, s0, c0, acc, u, pf[(k + 2) % D], vb0,
-                vb1, ops);
-            __syncthreads();
-            const int t = b_cur;
-            b_cur = b_next;
-            b_next = b_dec;
-            b_dec = t;
-        }
-    }
-
-    // ---- epilogue, one tile at a time -----------------------------------
-    // Chunk 0 (or the only chunk) writes the sums: plain stores (overwrite)
-    // or read-add-write (accumulate).  Later chunks store their tiles in the
-    // workspace and the merge kernel, launched next on the same stream, adds
-    // them: the kernel boundary orders the two, so no fence or counter is
-    // needed and the additions spread over the whole GPU.
-    // Halves geometry: waves 6 and 7 (odd steps) hand their sums to waves 4
-    // and 5 (even steps, the same tiles and layout) through LDS, which is
-    // free after the loop's last barrier; only waves 4 and 5 write.
-    if (kSmall) {
-        int32_t *cb = (int32_t *)lds + (wave & 1) * (8 * 16 * 64);
-        auto each = [&](auto fn) {
-            int m = 0;
-#pragma unroll
-            for (int k = 0; k < TL::NQ; ++k) fn(acc.q[k], m++);
-#pragma unroll
-            for (int k = 0; k < TL::NO; ++k) {
-                fn(acc.re[k], m++);
-                fn(acc.im[k], m++);
-            }
-        };
-        if (kMma && wave >= 6)
-            each([&](v16i &x, int m) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) cb[(m * 16 + v) * 64 + lane] = x[v];
-            });
-        __syncthreads();
-        if (kMma && (wave == 4 || wave == 5))
-            each([&](v16i &x, int m) {
-#pragma unroll
-                for (int v = 0; v < 16; ++v) x[v] += cb[(m * 16 + v) * 64 + lane];
-            });
-        __syncthreads();
-        if (!(kMma && (wave == 4 || wave == 5))) return;
-    }
-    constexpr int NT = TL::NT;
-    int32_t *tbuf = (int32_t *)lds + wave * (32 * 33);  // staging buffers are free now
-    const TileMap<SHAPE> map{g, s0, c0, a.N};
-    auto tile = [&](int k, v16i &re, v16i &im) {
-        if (k < TL::NQ) {
-            split_q(acc.q[k < TL::NQ ? k : 0], tbuf, re, im);
-        } else {
-            re = acc.re[k - TL::NQ];
-            im = acc.im[k - TL::NQ];
-        }
-    };
-    if (split > 0) {
-        const int64_t key = (int64_t)f * a.groups + gid;
-        int32_t *mine = partial_tiles(a.partials, key, a.splits, split, wave);
-#pragma unroll
-        for (int k = 0; k < NT; ++k) {
-            v16i re, im;
-            tile(k, re, im);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                v4i x = {re[4 * v], re[4 * v + 1], re[4 * v + 2], re[4 * v + 3]};
-                v4i y = {im[4 * v], im[4 * v + 1], im[4 * v + 2], im[4 * v + 3]};
-                *(v4i *)(mine + ((k * 8 + v) * 64 + lane) * 4) = x;
-                *(v4i *)(mine + ((k * 8 + 4 + v) * 64 + lane) * 4) = y;
-            }
-        }
-        return;
-    }
-    const int64_t P = (int64_t)a.N * (a.N + 1) / 2;
-    int32_t *visf = a.vis + (int64_t)f * P * 2;
-#pragma unroll
-    for (int k = 0; k < NT; ++k) {
-        // previous contents first (accumulate), all loads before any store
-        v2i old[16];
-        if (!kOverwrite) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t idx = map.elem(k, v, lane);
-                old[v] = idx >= 0 ? *(const v2i *)(visf + 2 * idx) : (v2i){0, 0};
-            }
-        }
-        v16i re, im;
-        tile(k, re, im);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t idx = map.elem(k, v, lane);
-            if (idx >= 0) {
-                v2i val = {re[v], im[v]};
-                *(v2i *)(visf + 2 * idx) = kOverwrite ? val : old[v] + val;
-            }
-        }
-    }
-}
-
-// Workgroup b runs on XCD b % 8 (round-robin dispatch); number the work so
-// that consecutive work items (the time chunks and groups of one channel)
-// share an XCD and its L2.
-__device__ __forceinline__ int64_t xcd_local_index(int64_t b, int64_t total) {
-    const int64_t per = total / 8, rem = total % 8;
-    const int64_t x = b % 8, idx = b / 8;
-    return x * per + (x < rem ? x : rem) + idx;
-}
-
-// One work item: tile group gid of channel f over time chunk `split`.
-// Every wave runs the same number of steps and barriers; the tile pattern is
-// fixed per group kind (blocks past N are staged as zeros).
-template <bool kAligned, bool kOverwrite, int KINDS = kAllKinds>
-__device__ __forceinline__ void run_item(const CorrArgs &a, int f, int gid, int split,
-                                         uint8_t *lds, uint32_t *mwords) {
-    const Group g = make_group(a.nb, gid, a.halves);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    with_role<KINDS>(g, wave, [&](auto role, int s0, int c0) {
-        using R = decltype(role);
-        run_wave<kAligned, kOverwrite, R::NSLOT, R::SHAPE, R::UPT, R::kMma, R::kSmall>(
-            a, g, f, gid, split, s0, c0, lds, mwords);
-    });
-}
-
-// One frame: workgroup -> (channel, group, chunk), groups of a channel
-// and chunks of a (channel, group) numbered next to each other.
-template <bool kAligned, bool kOverwrite>
-__global__ __launch_bounds__(kThreads, 1) void corr_kernel(CorrArgs a) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[3 * kBufBytes];
-    __shared__ uint32_t mwords[kMaskWindow];
-
-    const int G = a.groups;
-    const int64_t total = (int64_t)a.F * G * a.splits;
-    int64_t w = xcd_local_index(blockIdx.x, total);
-    const int gid = (int)(w % G);
-    w /= G;
-    const int split = (int)(w % a.splits);
-    const int f = (int)(w / a.splits);
-    run_item<kAligned, kOverwrite>(a, f, gid, split, lds, mwords);
-}
-
-// ---------------------------------------------------------------------------
-// batched persistent launch
-// ---------------------------------------------------------------------------
-
-// One correlator instance of a batch, as the kernel sees it.
-struct BatchInstance {
-    const uint8_t *packed;
-    const uint8_t *mask;
-    int32_t *vis;
-    int64_t *count;
-    int32_t N, F, T, B;
-    int32_t nblk_mask, nb, groups, splits;
-    int32_t steps_per_split, aligned;
-    int32_t halves, pad_;
-    int64_t partial_base;  // first int32 of its partial tiles
-};
-
-struct BatchItem {
-    int32_t inst, f, gid, split;
-};
-
-// A grid of one workgroup per CU pulls work items from a queue until it is
-// empty (every workgroup reaches the exit).  The last workgroup to finish
-// resets the queue, so the next launch of the same plan starts clean and
-// the launch can be replayed from a graph.  Items are accumulated into their
-// instances' resident sums.  Instances must take the dword-load path
-// (N % 4 == 0, 4-byte aligned frame); the host runs others on their own.
-// A batch has one list of items per geometry, each drained by its own
-// launch of this kernel (KINDS = kSuperOnly or kHalvesOnly).
-template <int KINDS>
-__global__ __launch_bounds__(kThreads, 1) void batch_kernel(const BatchInstance *inst,
-                                                            const BatchItem *items, int n_items,
-                                                            int *queue,
-                                                            int32_t *partials) {
-    __shared__ __attribute__((aligned(16))) uint8_t lds[3 * kBufBytes];
-    __shared__ uint32_t mwords[kMaskWindow];
-    __shared__ int s_item;
-    for (;;) {
-        __syncthreads();  // the previous item has released LDS
-        if (threadIdx.x == 0) s_item = atomicAdd(&queue[0], 1);
-        __syncthreads();
-        const int it = __builtin_amdgcn_readfirstlane(s_item);  // uniform: scalar loads below
-        if (it >= n_items) break;
-        // every field is wave-uniform: readfirstlane keeps them in scalar
-        // registers (buffer resources and offsets must live there)
-        auto u32 = [](int32_t v) { return (int32_t)__builtin_amdgcn_readfirstlane(v); };
-        auto u64 = [](int64_t v) {
-            uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-            uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
-            return (int64_t)(((uint64_t)hi << 32) | lo);
-        };
-        auto ptr = [&](const void *p) { return (void *)(uintptr_t)u64((int64_t)(uintptr_t)p); };
-        const BatchItem w = items[it];
-        const int wi = u32(w.inst), wf = u32(w.f), wg = u32(w.gid), ws = u32(w.split);
-        const BatchInstance &bi = inst[wi];
-        CorrArgs a;
-        a.packed = (const uint8_t *)ptr(bi.packed);
-        a.mask = (const uint8_t *)ptr(bi.mask);
-        a.vis = (int32_t *)ptr(bi.vis);
-        a.count = (int64_t *)ptr(bi.count);
-        a.partials = partials + u64(bi.partial_base);
-        a.N = u32(bi.N);
-        a.F = u32(bi.F);
-        a.T = u32(bi.T);
-        a.B = u32(bi.B);
-        a.nblk_mask = u32(bi.nblk_mask);
-        a.nb = u32(bi.nb);
-        a.groups = u32(bi.groups);
-        a.splits = u32(bi.splits);
-        a.steps_per_split = u32(bi.steps_per_split);
-        a.halves = u32(bi.halves);
-        run_item<true, false, KINDS>(a, wf, wg, ws, lds, mwords);
-    }
-    if (threadIdx.x == 0) {
-        int done = atomicAdd(&queue[1], 1);
-        if (done == (int)gridDim.x - 1) {
-            queue[0] = 0;
-            queue[1] = 0;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// merge of time chunks
-// ---------------------------------------------------------------------------
-
 // An instance whose time chunks are merged: chunk 0 has written its sums to
-// `vis`, chunks 1 .. splits-1 left their tiles in `partials`.
+// `vis`, chunks 1 .. splits-1 left theirs in copies of it, `stride` int32s
+// apart.
 struct MergeInst {
     int32_t *vis;
-    int32_t *partials;
-    int N, nb, groups, splits;
-    int halves, pad_;
+    const int32_t *partials;
+    int64_t ints;         // of one copy
+    int64_t stride;
+    int splits, pad_;
     int64_t block_begin;  // first merge block of the instance (batch lists)
 };
 
-// One wave adds chunks 1.. of tile k of its role in group `key` into vis;
-// the loads of three chunks and of the old sums are in flight together.
-template <int SHAPE>
-__device__ __forceinline__ void merge_tile(const MergeInst &m, const Group &g, int64_t key,
-                                           int wave, int k, int s0, int c0) {
-    using TL = Tiles<SHAPE>;
-    if (k >= TL::NT) return;
-    const int lane = threadIdx.x & 63;
-    const TileMap<SHAPE> map{g, s0, c0, m.N};
-    const int64_t f = key / m.groups;
-    const int64_t P = (int64_t)m.N * (m.N + 1) / 2;
-    int32_t *visf = m.vis + f * P * 2;
-    {
-        v2i old[16];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t idx = map.elem(k, v, lane);
-            old[v] = idx >= 0 ? *(const v2i *)(visf + 2 * idx) : (v2i){0, 0};
-        }
-        v16i re = (v16i){0}, im = (v16i){0};
-        for (int sp0 = 1; sp0 < m.splits; sp0 += 3) {
-            v4i ld[3][8];
-#pragma unroll
-            for (int jj = 0; jj < 3; ++jj) {
-                const int sp = sp0 + jj < m.splits ? sp0 + jj : 1;
-                const int32_t *src = partial_tiles(m.partials, key, m.splits, sp, wave) +
-                                     (k * 8 * 64 + lane) * 4;
-#pragma unroll
-                for (int v = 0; v < 8; ++v) ld[jj][v] = *(const v4i *)(src + v * 256);
-            }
-#pragma unroll
-            for (int jj = 0; jj < 3; ++jj) {
-                if (sp0 + jj < m.splits) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-#pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            re[4 * v + c] += ld[jj][v][c];
-                            im[4 * v + c] += ld[jj][4 + v][c];
-                        }
-                }
-            }
-        }
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int64_t idx = map.elem(k, v, lane);
-            if (idx >= 0) *(v2i *)(visf + 2 * idx) = old[v] + (v2i){re[v], im[v]};
-        }
-    }
-}
+constexpr int kMergeThreads = 256;
+constexpr int64_t kMergeInts = kMergeThreads * 4;   // int32s of a merge block
 
-// merge block b of an instance = (group key, wave role, tile) =
-// (b / (8 kTilesPerWave), b / kTilesPerWave % 8, b % kTilesPerWave)
-constexpr int kMergeBlocksPerGroup = kWaves * kTilesPerWave;
-
+// Block b of an instance adds its 16 bytes per thread of every copy; the
+// loads of four copies are in flight together.
 __device__ __forceinline__ void merge_block(const MergeInst &m, int64_t b) {
-    const int64_t key = b / kMergeBlocksPerGroup;
-    const int wave = (int)(b / kTilesPerWave % kWaves);
-    const int k = (int)(b % kTilesPerWave);
-    const Group g = make_group(m.nb, (int)(key % m.groups), m.halves);
-    if (g.small && wave != 4 && wave != 5) return;   // halves: waves 4 and 5 own the sums
-    with_role(g, wave, [&](auto role, int s0, int c0) {
-        merge_tile<decltype(role)::SHAPE>(m, g, key, wave, k, s0, c0);
-    });
+    const int64_t e = (b * kMergeThreads + threadIdx.x) * 4;
+    if (e >= m.ints) return;
+    const bool whole = e + 4 <= m.ints;   // else 2 are left (ints is even)
+    int32_t *o = m.vis + e;
+    v4i x;
+    if (whole) {
+        x = *(const v4i_a8 *)o;
+    } else {
+        const v2i y = *(const v2i *)o;
+        x = (v4i){y.x, y.y, 0, 0};
+    }
+    for (int s0 = 1; s0 < m.splits; s0 += 4) {
+        v4i v[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k)   // a copy's last 16 bytes lie inside its stride
+            v[k] = *(const v4i *)(m.partials +
+                                  (int64_t)(s0 + k < m.splits ? s0 + k - 1 : 0) * m.stride + e);
+#pragma unroll
+        for (int k = 0; k < 4; ++k)
+            if (s0 + k < m.splits) x += v[k];
+    }
+    if (whole)
+        *(v4i_a8 *)o = x;
+    else
+        *(v2i *)o = (v2i){x.x, x.y};
 }
 
-// one instance: F * groups * 8 * kTilesPerWave blocks of one wave
 // Valid-sample counts of a frame, taken by extra blocks of its merge launch
-// (block first_block + f counts channel f), so a chunked frame needs no
-// launch of its own for them.
+// (block first_block + k counts channels 4 k .. 4 k + 3, one per wave), so a
+// chunked frame needs no launch of its own for them.
 struct CountArgs {
     const uint8_t *mask;
     int64_t *count;
-    int nblk, B, T, overwrite;
+    int nblk, B, T, F, overwrite;
     int64_t first_block;
 };
 
-__global__ __launch_bounds__(64) void merge_kernel(MergeInst m, CountArgs c) {
+__global__ __launch_bounds__(kMergeThreads) void merge_kernel(MergeInst m, CountArgs c) {
     if ((int64_t)blockIdx.x >= c.first_block) {
-        const int f = (int)(blockIdx.x - c.first_block);
+        const int f = (int)(blockIdx.x - c.first_block) * (kMergeThreads / 64) +
+                      (int)(threadIdx.x >> 6);
+        if (f >= c.F) return;
         const int lane = threadIdx.x & 63;
         const int64_t n = valid_count(c.mask ? c.mask + (int64_t)f * c.nblk : nullptr, c.nblk,
                                       c.B, c.T, lane);
@@ -1028,7 +1503,7 @@ __global__ __launch_bounds__(64) void merge_kernel(MergeInst m, CountArgs c) {
 
 // a batch's chunked instances, sorted by block_begin; block b belongs to the
 // last instance whose first block is <= b
-__global__ __launch_bounds__(64) void merge_list_kernel(const MergeInst *list, int n) {
+__global__ __launch_bounds__(kMergeThreads) void merge_list_kernel(const MergeInst *list, int n) {
     const int64_t b = blockIdx.x;
     int lo = 0, hi = n - 1;
     while (lo < hi) {
@@ -1042,26 +1517,10 @@ __global__ __launch_bounds__(64) void merge_list_kernel(const MergeInst *list, i
     merge_block(m, b - m.block_begin);
 }
 
-// ---------------------------------------------------------------------------
-// valid-sample counts (the packet-loss counter, Sec. II-C)
-// ---------------------------------------------------------------------------
-
-// One wave per channel of one frame; a separate launch, so that the
-// correlation kernel's registers stay with its main loop.
+// The counts of every instance of a batch (block b = instance b, its waves
+// take its channels in turn); batches accumulate.
 constexpr int kCountWaves = 4;
 
-__global__ __launch_bounds__(64 * kCountWaves) void count_kernel(const uint8_t *mask, int nblk,
-                                                                 int B, int T, int F,
-                                                                 int64_t *count, int overwrite) {
-    const int lane = threadIdx.x & 63;
-    const int f = blockIdx.x * kCountWaves + (threadIdx.x >> 6);
-    if (f >= F) return;
-    const int64_t n = valid_count(mask ? mask + (int64_t)f * nblk : nullptr, nblk, B, T, lane);
-    if (lane == 0) count[f] = overwrite ? n : count[f] + n;
-}
-
-// The same for every instance of a batch (block b = instance b, its waves
-// take its channels in turn); batches accumulate.
 __global__ __launch_bounds__(64 * kCountWaves) void count_list_kernel(const BatchInstance *inst,
                                                                       int n_inst) {
     const BatchInstance &x = inst[blockIdx.x];

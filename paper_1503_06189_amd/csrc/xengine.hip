@@ -14,6 +14,7 @@
 
 #include "../../include/xengine.h"
 #include "plan.hpp"
+#include "short_kernels.hpp"
 #include "xcorr_kernels.hpp"
 #include "flag_kernels.hpp"
 #include "assemble_kernels.hpp"
@@ -118,10 +119,16 @@ xe_status check_frame(xe_handle h, const uint8_t *packed, int32_t N, int32_t F, 
     return XE_OK;
 }
 
-// Workspace: the tiles of time chunks 1 .. splits-1 of every chunked tile
-// group (chunk 0 writes the output directly), 327,680 B per group and chunk.
+// Workspace: a copy of the output for each of time chunks 1 .. splits-1 (chunk
+// 0 writes the output directly), counted as 327,680 B per tile group and
+// chunk, of which a copy takes at most 263,168.
 // The default leaves room for large batches and is small next to 288 GB.
 constexpr size_t kDefaultWorkspace = (size_t)1 << 30;
+
+// int32s of an output copy, rounded up so that every copy is 16-byte aligned
+int64_t copy_stride(int32_t N, int32_t F) {
+    return ((int64_t)F * N * (N + 1) + 3) / 4 * 4;
+}
 
 size_t partial_bytes(int64_t keys, int splits) {
     return splits > 1 ? (size_t)keys * (splits - 1) * xe::kGroupPartial * sizeof(int32_t) : 0;
@@ -165,6 +172,10 @@ bool fill_plan(int32_t N, int32_t F, int32_t T, int32_t n_cu, size_t ws_bytes, i
     return splits == 1 || partial_bytes(keys, splits) <= ws_bytes;
 }
 
+int64_t merge_blocks(int64_t ints) {
+    return (ints + xe::kMergeInts - 1) / xe::kMergeInts;
+}
+
 // Where a correlation call keeps the partial sums of its time chunks: the
 // handle's workspace, or the static scratch array of the allocation-free
 // entry point.  `h` (may be null) receives the error text.
@@ -197,40 +208,50 @@ xe_status launch_corr(xe_handle h, const Scratch &ws, const uint8_t *packed, con
     a.groups = p.groups;
     a.splits = p.splits;
     a.steps_per_split = p.steps_per_split;
-    a.halves = halves;
+    a.partial_stride = copy_stride(N, F);
+    a.overwrite = overwrite ? 1 : 0;
     if (p.workgroups > 0x7fffffff) return fail(h, XE_ERR_ARG, "too many workgroups");
-    dim3 grid((unsigned)p.workgroups), block(xe::kThreads);
-    bool al = aligned(packed, 4) && (N % 4 == 0);
-    if (al && overwrite)
-        hipLaunchKernelGGL((xe::corr_kernel<true, true>), grid, block, 0, stream, a);
-    else if (al)
-        hipLaunchKernelGGL((xe::corr_kernel<true, false>), grid, block, 0, stream, a);
-    else if (overwrite)
-        hipLaunchKernelGGL((xe::corr_kernel<false, true>), grid, block, 0, stream, a);
+    const bool small = xe::use_halves(halves, p.blocks);
+    dim3 grid((unsigned)p.workgroups), block(small ? xe::kSmallThreads : xe::kSuperThreads);
+    // (a frame of less than 4 bytes: the int8 kernel's unaligned loads need 4)
+    const bool brief =
+        xe::use_short(small, p.steps_per_split) && (int64_t)T * F * N >= 4;
+    // The valid-sample counts of a chunked frame come from extra blocks of the
+    // merge launch; an unchunked one's workgroups count what they integrate.
+    if (p.splits > 1) a.count = nullptr;
+    if (brief) {
+        const bool al = aligned(packed, 4) && N % 4 == 0;
+        const dim3 threads(xe::brief::kThreads);
+        if (al && overwrite)
+            hipLaunchKernelGGL((xe::brief::corr_kernel<true, true>), grid, threads, 0, stream, a,
+                               (int)small);
+        else if (al)
+            hipLaunchKernelGGL((xe::brief::corr_kernel<true, false>), grid, threads, 0, stream, a,
+                               (int)small);
+        else if (overwrite)
+            hipLaunchKernelGGL((xe::brief::corr_kernel<false, true>), grid, threads, 0, stream, a,
+                               (int)small);
+        else
+            hipLaunchKernelGGL((xe::brief::corr_kernel<false, false>), grid, threads, 0, stream, a,
+                               (int)small);
+    }
+    else if (small)
+        hipLaunchKernelGGL(xe::corr_kernel<true>, grid, block, 0, stream, a);
     else
-        hipLaunchKernelGGL((xe::corr_kernel<false, false>), grid, block, 0, stream, a);
-    // The valid-sample counts run outside the correlation kernel, so that
-    // its registers stay with its main loop: in extra blocks of the merge
-    // launch when the frame is chunked, else in a launch of their own.
-    if (p.splits == 1)
-        hipLaunchKernelGGL(xe::count_kernel,
-                           dim3((unsigned)((F + xe::kCountWaves - 1) / xe::kCountWaves)),
-                           dim3(64 * xe::kCountWaves), 0, stream, mask, a.nblk_mask, B, T, F,
-                           count, overwrite ? 1 : 0);
+        hipLaunchKernelGGL(xe::corr_kernel<false>, grid, block, 0, stream, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "correlation launch");
     if (p.splits > 1) {
-        // chunks 1.. into the output; stream order makes their tiles visible
+        // chunks 1.. into the output; stream order makes their sums visible
         xe::MergeInst m;
         m.vis = vis;
         m.partials = a.partials;
-        m.N = N;
-        m.nb = p.blocks;
-        m.groups = p.groups;
+        m.ints = (int64_t)F * N * (N + 1);
+        m.stride = a.partial_stride;
         m.splits = p.splits;
-        m.halves = halves;
+        m.pad_ = 0;
         m.block_begin = 0;
-        const int64_t blocks = (int64_t)F * p.groups * xe::kMergeBlocksPerGroup;
+        const int64_t blocks = merge_blocks(m.ints);
         if (blocks + F > 0x7fffffff) return fail(h, XE_ERR_ARG, "too many merge blocks");
         xe::CountArgs c;
         c.mask = mask;
@@ -238,10 +259,12 @@ xe_status launch_corr(xe_handle h, const Scratch &ws, const uint8_t *packed, con
         c.nblk = a.nblk_mask;
         c.B = B;
         c.T = T;
+        c.F = F;
         c.overwrite = overwrite ? 1 : 0;
         c.first_block = blocks;
-        hipLaunchKernelGGL(xe::merge_kernel, dim3((unsigned)(blocks + F)), dim3(64), 0, stream, m,
-                           c);
+        const int per = xe::kMergeThreads / 64;
+        hipLaunchKernelGGL(xe::merge_kernel, dim3((unsigned)(blocks + (F + per - 1) / per)),
+                           dim3(xe::kMergeThreads), 0, stream, m, c);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(h, e, "merge launch");
     }
@@ -270,7 +293,7 @@ struct BatchPlan {
     std::vector<int64_t> merge_base;    // their first partial value in the workspace
     int chunk_steps = 0;
     int64_t partials = 0;      // int32 partial values used
-    int64_t merge_blocks = 0;  // one-wave blocks of the merge pass
+    int64_t merge_blocks = 0;  // blocks of the merge pass
 };
 
 size_t plan_bytes(const BatchPlan &p) {
@@ -377,24 +400,21 @@ xe_status fill_batch(xe_handle h, const xe_instance *inst, int32_t n_inst, int32
         b.groups = G;
         b.splits = splits;
         b.steps_per_split = sps;
-        b.aligned = 1;
-        b.halves = halves;
         b.pad_ = 0;
         b.partial_base = plan->partials;
+        b.partial_stride = copy_stride(x.N, x.F);
         if (splits > 1) {
             xe::MergeInst m;
             m.vis = x.vis;
             m.partials = nullptr;  // set from the workspace at launch
-            m.N = x.N;
-            m.nb = nb;
-            m.groups = G;
+            m.ints = (int64_t)x.F * x.N * (x.N + 1);
+            m.stride = b.partial_stride;
             m.splits = splits;
-            m.halves = halves;
             m.pad_ = 0;
             m.block_begin = plan->merge_blocks;
             plan->merges.push_back(m);
             plan->merge_base.push_back(plan->partials);
-            plan->merge_blocks += (int64_t)x.F * G * xe::kMergeBlocksPerGroup;
+            plan->merge_blocks += merge_blocks(m.ints);
             plan->partials += (int64_t)x.F * G * (splits - 1) * xe::kGroupPartial;
         }
         const int idx = (int)plan->inst.size();
@@ -462,20 +482,20 @@ xe_status launch_batch(xe_handle h, int slot, const SlotShape &sh, hipStream_t s
     const xe::MergeInst *merges = (const xe::MergeInst *)(small + sh.n_small);
     int *queues = (int *)base;   // [0, 1]: super-block items, [2, 3]: halves items
     if (sh.n_items > 0)
-        hipLaunchKernelGGL(xe::batch_kernel<xe::kSuperOnly>, dim3(std::min(h->n_cu, sh.n_items)),
-                           dim3(xe::kThreads), 0, stream, bi, items, sh.n_items, queues,
+        hipLaunchKernelGGL(xe::batch_kernel<false>, dim3(std::min(h->n_cu, sh.n_items)),
+                           dim3(xe::kSuperThreads), 0, stream, bi, items, sh.n_items, queues,
                            (int32_t *)h->workspace);
     if (sh.n_small > 0)
-        hipLaunchKernelGGL(xe::batch_kernel<xe::kHalvesOnly>,
-                           dim3(std::min(h->n_cu, sh.n_small)), dim3(xe::kThreads), 0, stream, bi,
+        hipLaunchKernelGGL(xe::batch_kernel<true>,
+                           dim3(std::min(h->n_cu, sh.n_small)), dim3(xe::kSmallThreads), 0, stream, bi,
                            small, sh.n_small, queues + 2, (int32_t *)h->workspace);
     hipLaunchKernelGGL(xe::count_list_kernel, dim3((unsigned)sh.n_inst),
                        dim3(64 * xe::kCountWaves), 0, stream, bi, sh.n_inst);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "batch launch");
     if (sh.n_merges > 0) {
-        hipLaunchKernelGGL(xe::merge_list_kernel, dim3((unsigned)sh.merge_blocks), dim3(64), 0,
-                           stream, merges, sh.n_merges);
+        hipLaunchKernelGGL(xe::merge_list_kernel, dim3((unsigned)sh.merge_blocks),
+                           dim3(xe::kMergeThreads), 0, stream, merges, sh.n_merges);
         e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(h, e, "batch merge launch");
     }
