@@ -9,26 +9,41 @@
 // the host, listing the flagged inputs of every sample, O(E^2) per sample.
 // Here d, diagonal included, is one 0/1 Gram matrix per channel,
 //     D = A A^T over valid samples,  A[i][t] = flag bit of input i at t,
-// on the int8 matrix cores: exact, and its cost does not grow with the
-// number of points a sample flags.
+// on the matrix cores: exact, and its cost does not grow with the number of
+// points a sample flags.
 //
 // Flags arrive as bit-fields flags[f][t][w], W = ceil(N/32) words, bit i % 32
-// of word i / 32 = input i.  A workgroup takes one channel, one pair of
-// 256-input super blocks (R <= C) and one chunk of time; its waves take the
-// chunk's 32-sample steps in turn and never wait for each other:
-//   1. a wave loads the words of its next 8 steps at once (0 for lost
-//      samples, samples past the chunk and inputs past N) and finds, with one
-//      ballot per word, which 32-input blocks hold a flag in each step; a
-//      step without any ends there, the counterpart of the method's test of
-//      whole 32-bit words before extracting bits;
-//   2. for a flagged step, the wave turns every flagged block's 32 x 32 bits
-//      into the operand of v_mfma_i32_32x32x32_i8 (lane l: input l % 32, 16
-//      samples of half l / 32 as 0/1 bytes) by byte selection and a shift,
-//      and runs one MFMA per tile whose two blocks both hold a flag;
-//   3. the tile's counts are added into the workgroup's LDS counts (16 bits
-//      each, two per word), and at the end the nonzero ones into d with
-//      integer atomics, so the order of waves and chunks does not matter.
-// A chunk without any flag costs only its loads.
+// of word i / 32 = input i.  A workgroup of eight waves takes one channel,
+// 8 or 10 tiles of 32 x 32 counts (a unit: the triangle of a 128-input group,
+// or half a group's rows against another group) and one chunk of time; its
+// waves take the chunk's K-steps of 64 samples in turn and never wait for
+// each other:
+//   1. a wave loads the unit's 4 or 6 words of a sample per lane (0 for lost
+//      samples, samples past the chunk and inputs past N), a batch of
+//      four K-steps ahead; a K-step without a flag on both sides of its tiles
+//      ends there, the counterpart of the method's test of whole 32-bit words
+//      before extracting bits;
+//   2. a word with a flag becomes a matrix operand: its 64 lanes' 32 x 32 bits
+//      (two halves) are transposed across the lanes in five exchange steps,
+//      after which lane l holds 32 samples of input l % 32 in one dword, and
+//      seven vector instructions expand that into 4-bit codes (code 2 is 1.0);
+//   3. v_mfma_f32_32x32x64_f8f6f4 counts 64 samples of every tile whose two
+//      words both hold a flag.  The counts stay in registers: float32 is
+//      exact up to 2^24, a chunk has at most 32,768 samples;
+//   4. at the chunk's end the waves' counts are added in LDS (16 bits each,
+//      four per word), and the nonzero ones into d: a unit's only chunk owns
+//      its counts and adds them plainly, several chunks use integer atomics,
+//      whose order does not matter.
+// What bounds it: sparse flags cost their loads, 33.6 MB for 256 inputs, 64
+// channels and 16,384 samples (zeroing and counting 17.6 us with bursts over
+// 0.1% of the points); scattered flags (5%) the vector instructions of the
+// transposes: 512 inputs, 32 channels, 8,192 samples take 53 us, where adding
+// the counts of every 32-sample step into LDS on their own took 449 us, the
+// LDS atomics' rate.  The units are this small, although their words are
+// loaded and transposed 2.5 times, because a channel's counts then come from
+// one chunk: with 36 tiles to a workgroup and four chunks to a channel the
+// global atomics took 34 of 59 us (256 dense inputs).  Many inputs: see
+// flag_wide_kernels.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -39,19 +54,23 @@
 namespace xe {
 namespace flag {
 
+typedef int v2i __attribute__((ext_vector_type(2)));
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
+typedef int v8i __attribute__((ext_vector_type(8)));
+typedef float v16f __attribute__((ext_vector_type(16)));
 
-constexpr int kSuper = 8;           // 32-input blocks per super block
 constexpr int kWindow = 1024;       // validity words per chunk: chunks <= 32768 samples
+constexpr int kWaves = 8, kThreads = 64 * kWaves;
+constexpr int kBatch = 4;           // K-steps a wave loads at once
 
 struct Args {
     const uint32_t *flags;   // [F][T][W]
     const uint8_t *mask;     // [F][nblk], may be null
     int32_t *d;              // [F][P]
     int N, F, T, B, W, nblk;
+    int groups;              // 128-input groups, ceil(N / 128)
     int ns;                  // super blocks, ceil(N / 256)
-    int chunks;              // time chunks per (channel, pair)
+    int chunks;              // time chunks per (channel, unit or pair)
     int chunk_samples;       // samples per chunk, a multiple of 32, <= 32 kWindow
     uint64_t b_magic;        // ceil(2^40 / B) when B <= 2^16, else 0
 };
@@ -63,88 +82,101 @@ __device__ __forceinline__ int block_of(const Args &a, int t) {
     return a.b_magic ? (int)(((uint64_t)(uint32_t)t * a.b_magic) >> 40) : t / a.B;
 }
 
-// A diagonal pair (R == C) has 36 tiles of 32 x 32 counts (blocks bi <= bj)
-// and runs 16 waves; an off-diagonal pair (R < C) has 64 and runs 8 waves,
-// and every wave loads the words of both super blocks.
-template <bool kOff>
-struct Shape {
-    static constexpr int kSides = kOff ? 2 : 1;
-    static constexpr int kWaves = kOff ? 8 : 16;
-    static constexpr int kThreads = 64 * kWaves;
-    static constexpr int kTiles = kOff ? 64 : 36;
-    static constexpr int kBatch = kOff ? 4 : 8;   // steps a wave loads before it uses the first
-    static constexpr int kPitch = kOff ? 8 : 9;   // 64-bit words per tile column in LDS
-    static constexpr int kTileQuads = 32 * kPitch;
+// Counts of the chunk in LDS as four 16-bit fields per 64-bit word (no field
+// carries into the next): tile k, column j, rows 4 Q .. 4 Q + 3 at
+// acc[k * kTile + j * kPitch + Q], row 4 Q in the low field.  The odd pitch
+// spreads lanes along j over the banks.
+constexpr int kPitch = 9, kTile = 32 * kPitch, kMaxTiles = 10;
+struct Lds {
+    uint64_t acc[kMaxTiles * kTile];
+    uint32_t valid[kWindow];        // bit k of word s: sample 32 s + k of the chunk
 };
 
-// Counts of the chunk in LDS as four 16-bit fields per 64-bit word (a chunk
-// holds at most 32768 samples, so no field carries into the next): tile k,
-// column j, rows 4 Q .. 4 Q + 3 at acc[k][j * kPitch + Q], row 4 Q in the
-// low field.  The diagonal pair's odd pitch spreads the two half-waves of
-// an MFMA result over different banks.
-template <bool kOff>
-struct Lds {
-    using S = Shape<kOff>;
-    uint64_t acc[S::kTiles * S::kTileQuads];
-    uint32_t words[S::kWaves][S::kSides][kSuper][32];  // per wave: its current step
-    uint32_t valid[kWindow];   // bit k of word s: sample 32 s + k of the chunk
-};
+__device__ __forceinline__ uint32_t uniform(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
 
 __device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
     return __builtin_amdgcn_perm(hi, lo, sel);
-}
-
-__device__ __forceinline__ v16i mfma(v4i a, v4i b, v16i c) {
-    return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0);
 }
 
 __device__ __forceinline__ int64_t tri(int64_t N, int64_t i, int64_t j) {
     return i * N - i * (i - 1) / 2 + (j - i);
 }
 
-// Operand of block b of one step, from the 32 words of its samples
-// (src[t] = word of sample t): byte q of this lane's 16 is the flag of input
-// l % 32 at sample 16 (l / 32) + q.  Each group of 4 words gives one dword:
-// byte (i / 8) of each word is gathered with two byte permutes, then bit
-// (i % 8) of every byte is shifted down and masked.
-__device__ __forceinline__ v4i build_op(const uint32_t *src, int lane) {
-    const int i = lane & 31, h = lane >> 5;
-    const uint32_t bi = (uint32_t)(i >> 3), bb = (uint32_t)(i & 7);
-    const uint32_t sel_lo = 0x0c0c0000u | ((4u + bi) << 8) | bi;
-    const uint32_t sel_hi = ((4u + bi) << 24) | (bi << 16) | 0x0c0cu;
-    const v4i *p = (const v4i *)(src + h * 16);
-    v4i out;
-#pragma unroll
-    for (int d = 0; d < 4; ++d) {
-        const v4i w = p[d];
-        const uint32_t x = perm((uint32_t)w.y, (uint32_t)w.x, sel_lo) |
-                           perm((uint32_t)w.w, (uint32_t)w.z, sel_hi);
-        out[d] = (int)((x >> bb) & 0x01010101u);
+// A 32 x 32 bit transpose in each half-wave (lane = sample, bit = input before,
+// lane = input, bit = sample after) exchanges every bit of the lane number
+// with one of the bit number, five steps of 14 vector instructions in all.  A
+// step pairs lanes that cross-lane moves reach without the LDS: l and l ^ 16,
+// 8, 7, 2, 1.  With 7 in place of 4 the lane's number in the steps is
+// l ^ 3 where bit 2 is set: lane l ends up with input shuffled(l).
+__device__ __forceinline__ int shuffled(int l) { return l ^ ((l & 4) != 0 ? 3 : 0); }
+
+struct Transpose {
+    uint32_t sel16, sel8, by4, keep4, by2, keep2, by1, keep1;
+
+    __device__ __forceinline__ explicit Transpose(int lane) {
+        const int n = shuffled(lane);
+        sel16 = n & 16 ? 0x03020706u : 0x01000504u;
+        sel8 = n & 8 ? 0x07030501u : 0x02060004u;
+        by4 = n & 4 ? 4 : 28;
+        keep4 = n & 4 ? 0xf0f0f0f0u : 0x0f0f0f0fu;
+        by2 = n & 2 ? 2 : 30;
+        keep2 = n & 2 ? 0xccccccccu : 0x33333333u;
+        by1 = n & 1 ? 1 : 31;
+        keep1 = n & 1 ? 0xaaaaaaaau : 0x55555555u;
     }
-    return out;
+    // the other lane's bits into the places that `keep` leaves
+    template <int DPP>
+    __device__ __forceinline__ static uint32_t step(uint32_t x, uint32_t by, uint32_t keep) {
+        const uint32_t y = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, DPP, 0xf, 0xf, true);
+        return (x & keep) | (__builtin_amdgcn_alignbit(y, y, by) & ~keep);
+    }
+    __device__ __forceinline__ uint32_t operator()(uint32_t x) const {
+        // the even rows of 16 lanes twice, and the odd ones
+        const auto s = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+        x = perm(s[0], s[1], sel16);
+        const uint32_t y = (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x128, 0xf, 0xf, true);   // + 8
+        x = perm(x, y, sel8);
+        x = step<0x141>(x, by4, keep4);         // half rows mirrored: l ^ 7
+        x = step<0x4e>(x, by2, keep2);          // quads 2 3 0 1
+        return step<0xb1>(x, by1, keep1);       // 1 0 3 2
+    }
+};
+
+// 32 flag bits as 4-bit codes: 2 (1.0) for a flag.  The samples' order inside
+// K is the same for every operand.
+__device__ __forceinline__ v4i expand(uint32_t x) {
+    return (v4i){(int)((x << 1) & 0x22222222u), (int)(x & 0x22222222u),
+                 (int)((x >> 1) & 0x22222222u), (int)((x >> 2) & 0x22222222u)};
+}
+__device__ __forceinline__ v16f mfma(v4i a, v4i b, v16f c) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+        __builtin_shufflevector(a, a, 0, 1, 2, 3, -1, -1, -1, -1),
+        __builtin_shufflevector(b, b, 0, 1, 2, 3, -1, -1, -1, -1), c, 4, 4, 0, 0, 0, 0);
 }
 
-// Add a 32 x 32 block of counts (an MFMA result: element v at row
-// 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32) into LDS tile `t`, four rows
-// per 64-bit word.
-template <int PITCH>
-__device__ __forceinline__ void add_tile(uint64_t *t, const v16i &c, int lane) {
-    uint64_t *col = t + (lane & 31) * PITCH + (lane >> 5);
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint64_t lo = (uint32_t)c[4 * q] | ((uint32_t)c[4 * q + 1] << 16);
-        const uint64_t hi = (uint32_t)c[4 * q + 2] | ((uint32_t)c[4 * q + 3] << 16);
-        atomicAdd((unsigned long long *)(col + 2 * q), (unsigned long long)(lo | (hi << 32)));
+// Tile k of a unit pairs its words row(k) and col(k).  A triangle's words are
+// the four blocks of its group; a rectangle's two blocks of rows, then four
+// of columns.
+template <bool kTri>
+struct Unit {
+    static constexpr int kWords = kTri ? 4 : 6, kTiles = kTri ? 10 : 8;
+    __device__ static constexpr int row(int k) {
+        return !kTri ? k >> 2 : k < 4 ? 0 : k < 7 ? 1 : k < 9 ? 2 : 3;
     }
-}
+    __device__ static constexpr int col(int k) {
+        return !kTri ? 2 + (k & 3) : k < 4 ? k : k < 7 ? k - 3 : k < 9 ? k - 5 : 3;
+    }
+};
 
 // Validity of the chunk's samples, one bit each, in LDS: 1 inside the chunk
 // and outside lost blocks.  All threads take part; a barrier must follow.
-template <bool kOff>
-__device__ __forceinline__ void fill_window(const Args &a, Lds<kOff> &L, int f, int t_begin,
+template <int kThreads>
+__device__ __forceinline__ void fill_window(const Args &a, uint32_t *valid, int f, int t_begin,
                                             int t_end, int tid) {
     const int words = (t_end - t_begin + 31) >> 5;
-    for (int s = tid; s < words; s += Shape<kOff>::kThreads) {
+    for (int s = tid; s < words; s += kThreads) {
         const int t = t_begin + 32 * s;
         const int n = min(32, t_end - t);
         uint32_t bits = n == 32 ? 0xffffffffu : (1u << n) - 1u;
@@ -168,36 +200,8 @@ __device__ __forceinline__ void fill_window(const Args &a, Lds<kOff> &L, int f, 
                 }
             }
         }
-        L.valid[s] = bits;
+        valid[s] = bits;
     }
-}
-
-// The words of kBatch steps, step q at byte row0 + q * step_bytes of the
-// buffer (steps past its range read 0), all loads issued before any is
-// used: four dwords per side, or one 16-byte load when kVec (the four words
-// of a side are contiguous and 16-byte aligned).
-template <bool kVec, int kBatch, int SIDES>
-__device__ __forceinline__ void load_batch(uint32_t (&raw)[kBatch][SIDES][4],
-                                           __amdgpu_buffer_rsrc_t rsrc,
-                                           const uint32_t (&off)[SIDES][4], uint32_t row0,
-                                           uint32_t step_bytes) {
-#pragma unroll
-    for (int q = 0; q < kBatch; ++q)
-#pragma unroll
-        for (int side = 0; side < SIDES; ++side) {
-            const uint32_t o = row0 + q * step_bytes;
-            if (kVec) {
-                const v4i v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(o + off[side][0]),
-                                                                    0, 0);
-#pragma unroll
-                for (int r = 0; r < 4; ++r) raw[q][side][r] = (uint32_t)v[r];
-            } else {
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    raw[q][side][r] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(
-                        rsrc, (int)(o + off[side][r]), 0, 0);
-            }
-        }
 }
 
 // Workgroup b runs on XCD b % 8; consecutive work items (the chunks of one
@@ -208,194 +212,229 @@ __device__ __forceinline__ int64_t xcd_local(int64_t b, int64_t total) {
     return x * per + (x < rem ? x : rem) + idx;
 }
 
-// One workgroup: channel f, super-block pair (R, C), one time chunk.  Every
-// wave takes its own 32-sample steps of the chunk (wave, wave + waves, ...),
-// kBatch steps' loads in flight at once (the first batch issued before the
-// workgroup's set-up), and never waits for another wave:
-//   * lane l holds sample l / 2 of the step and words 4 (l % 2) .. +3 of
-//     each super block, masked by the sample's validity and the inputs < N;
-//   * one ballot tells whether the step holds any flag; a step without any
-//     (the common case for the sparse flags of the method) ends there, the
-//     counterpart of the method's test of whole 32-bit words;
-//   * otherwise one ballot per word tells which 32-input blocks hold a flag,
-//     the wave stores the step's words in its own LDS slot, builds the MFMA
-//     operand of every flagged block, and runs one v_mfma_i32_32x32x32_i8 per
-//     tile whose two blocks both hold a flag, adding the 32 x 32 counts into
-//     the workgroup's LDS counts.
-// After a barrier, the nonzero counts are added into d with integer atomics
-// (time chunks of one pair add into the same counts; the order does not
-// matter).
-template <bool kOff, bool kVec>
-__global__ __launch_bounds__(Shape<kOff>::kThreads) void gram_kernel(Args a) {
-    using S = Shape<kOff>;
-    constexpr int SIDES = S::kSides;
-    __shared__ __attribute__((aligned(16))) Lds<kOff> L;
+template <bool kTri>
+struct Wave {
+    using U = Unit<kTri>;
+    Lds &L;
+    Transpose transpose;
+    __amdgpu_buffer_rsrc_t rsrc;
+    int lane, wave, samples;
+    uint32_t row_bytes, at, at_rows;   // byte offsets of the lane's words in K-step `wave`
+    v4i pad;                           // the bits of inputs < N of the column words
+    v4i raw[kBatch];                   // column words of the next batch
+    v2i raw_rows[kBatch];              // row words (rectangle)
+    v4i now[kBatch];                   // of this one, masked
+    uint32_t row0[kBatch], row1[kBatch];
+    v4i op[U::kWords];
+    v16f acc[U::kTiles];
+    uint32_t seen;                     // words that held a flag to count
+
+    // sample of K-step q of batch b, lane 0 (ascending; a batch is one K-step
+    // of every wave, kBatch times)
+    __device__ __forceinline__ int sample(int b, int q) const {
+        return 64 * (wave + kWaves * (kBatch * b + q));
+    }
+    template <int Q>
+    __device__ __forceinline__ void load(int b) {
+        if constexpr (Q < kBatch) {
+            const uint32_t o = (uint32_t)(64 * kWaves * (kBatch * b + Q)) * row_bytes;
+            raw[Q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)(at + o), 0, 0);
+            if constexpr (!kTri)
+                raw_rows[Q] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, (int)(at_rows + o), 0, 0);
+            load<Q + 1>(b);
+        }
+    }
+    // masks K-step Q's words; bit Q of the result: its tiles have a flag to count
+    template <int Q>
+    __device__ __forceinline__ uint32_t look(int b) {
+        if constexpr (Q < kBatch) {
+            const int t = sample(b, Q) + lane;
+            // (past the chunk the words are 0)
+            const uint32_t valid = L.valid[(t >> 5) & (kWindow - 1)];
+            const int keep = -(int)((valid >> (t & 31)) & 1u);
+            const v4i w = raw[Q] & pad & (v4i){keep, keep, keep, keep};
+            now[Q] = w;
+            bool some = __ballot((w.x | w.y | w.z | w.w) != 0) != 0;
+            if constexpr (!kTri) {
+                const v2i y = raw_rows[Q];
+                row0[Q] = (uint32_t)(y.x & keep);
+                row1[Q] = (uint32_t)(y.y & keep);
+                some = some && __ballot((row0[Q] | row1[Q]) != 0u) != 0;
+            }
+            return (some ? 1u << Q : 0u) | look<Q + 1>(b);
+        } else {
+            return 0u;
+        }
+    }
+    template <int Q>
+    __device__ __forceinline__ void take(uint32_t (&w)[U::kWords], int q) const {
+        if constexpr (Q < kBatch) {
+            if (q == Q) {
+                // (The asm differs between branches: else the compiler merges
+                // their loads into one from a chosen address, and everything
+                // stays in memory.)
+                v4i c = now[Q];
+                asm volatile("; step %1" : "+v"(c) : "i"(Q));
+                if constexpr (!kTri) {
+                    uint32_t x = row0[Q], y = row1[Q];
+                    asm volatile("; step %2" : "+v"(x), "+v"(y) : "i"(Q));
+                    w[0] = x;
+                    w[1] = y;
+                }
+                w[U::kWords - 4] = (uint32_t)c.x;
+                w[U::kWords - 3] = (uint32_t)c.y;
+                w[U::kWords - 2] = (uint32_t)c.z;
+                w[U::kWords - 1] = (uint32_t)c.w;
+            } else {
+                take<Q + 1>(w, q);
+            }
+        }
+    }
+    template <int I>
+    __device__ __forceinline__ uint32_t operands(const uint32_t (&w)[U::kWords]) {
+        if constexpr (I < U::kWords) {
+            uint32_t flagged = 0;
+            if (__ballot(w[I] != 0u) != 0) {
+                op[I] = expand(transpose(w[I]));
+                flagged = 1u << I;
+            }
+            return flagged | operands<I + 1>(w);
+        } else {
+            return 0u;
+        }
+    }
+    template <int K>
+    __device__ __forceinline__ void count(uint32_t flagged) {
+        if constexpr (K < U::kTiles) {
+            constexpr uint32_t both = 1u << U::row(K) | 1u << U::col(K);
+            if ((flagged & both) == both) acc[K] = mfma(op[U::row(K)], op[U::col(K)], acc[K]);
+            count<K + 1>(flagged);
+        }
+    }
+    // batch b: its words have been requested; those of the next one are
+    __device__ __forceinline__ void batch(int b) {
+        uint32_t todo = uniform(look<0>(b));
+        load<0>(b + 1);
+#pragma clang loop unroll(disable)
+        while (todo != 0) {
+            const int q = __builtin_ctz(todo);
+            todo &= todo - 1;
+            uint32_t w[U::kWords];
+            take<0>(w, q);
+            const uint32_t flagged = uniform(operands<0>(w));
+            seen |= flagged;
+            count<0>(flagged);
+        }
+    }
+    // Adds the wave's counts into LDS: element v of a tile is at row
+    // 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32, both of shuffled inputs.
+    template <int K>
+    __device__ __forceinline__ void add_tiles() {
+        if constexpr (K < U::kTiles) {
+            constexpr uint32_t both = 1u << U::row(K) | 1u << U::col(K);
+            if ((seen & both) == both) {
+                uint64_t *t = L.acc + K * kTile + shuffled(lane & 31) * kPitch + (lane >> 5);
+                const bool odd = lane >= 32;   // rows 4 .. 7 of 8: in reverse
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const uint32_t x0 = (uint32_t)acc[K][4 * g], x1 = (uint32_t)acc[K][4 * g + 1];
+                    const uint32_t x2 = (uint32_t)acc[K][4 * g + 2], x3 = (uint32_t)acc[K][4 * g + 3];
+                    const uint32_t lo = odd ? x3 | x2 << 16 : x0 | x1 << 16;
+                    const uint32_t hi = odd ? x1 | x0 << 16 : x2 | x3 << 16;
+                    atomicAdd((unsigned long long *)(t + 2 * g),
+                              (unsigned long long)(lo | ((uint64_t)hi << 32)));
+                }
+            }
+            add_tiles<K + 1>();
+        }
+    }
+};
+
+// A unit: first word of its rows and of its columns (a triangle: the same).
+template <bool kTri>
+__device__ __forceinline__ void run_unit(const Args &a, Lds &L, int f, int row_word, int col_word,
+                                         int t_begin, int t_end) {
+    using U = Unit<kTri>;
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63;
-    const int pairs = kOff ? a.ns * (a.ns - 1) / 2 : a.ns;
-    const int64_t total = (int64_t)a.F * pairs * a.chunks;
-    const int64_t w = xcd_local(blockIdx.x, total);
-    const int chunk = (int)(w % a.chunks);
-    const int64_t rest = w / a.chunks;
-    const int g = (int)(rest % pairs);
-    const int f = __builtin_amdgcn_readfirstlane((int)(rest / pairs));
-    int R = g, C = g;
-    if (kOff) {
-        // g -> (R, C), R < C, row-major over the strict upper triangle
-        int rem = g;
-        R = 0;
-        while (rem >= a.ns - 1 - R) {
-            rem -= a.ns - 1 - R;
-            ++R;
-        }
-        C = R + 1 + rem;
-    }
-    R = __builtin_amdgcn_readfirstlane(R);
-    C = __builtin_amdgcn_readfirstlane(C);
-    const int t_begin = __builtin_amdgcn_readfirstlane(chunk * a.chunk_samples);
-    const int t_end = __builtin_amdgcn_readfirstlane(min(a.T, t_begin + a.chunk_samples));
-    const int nsteps = (t_end - t_begin + 31) >> 5;
-
+    Wave<kTri> w = {L, Transpose(tid & 63)};
+    w.lane = tid & 63;
+    w.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    w.samples = t_end - t_begin;
+    w.seen = 0;
     // the chunk's rows of this channel's flags through a buffer resource
-    // whose range ends at the chunk's last sample: loads past it return 0
+    // whose range ends at the chunk's last sample: dwords past it read 0
     // without a memory access
-    const uint32_t row_bytes = 4u * (uint32_t)a.W;
+    w.row_bytes = 4u * (uint32_t)a.W;
     const uint64_t base = (uint64_t)(uintptr_t)(a.flags + ((int64_t)f * a.T + t_begin) * a.W);
-    const uint32_t extent =
-        __builtin_amdgcn_readfirstlane((uint32_t)(t_end - t_begin) * row_bytes);
-    // (readfirstlane returns int: both halves go through uint32_t so the low
-    // one is not sign-extended into the high one)
-    const uint32_t base_lo = __builtin_amdgcn_readfirstlane((uint32_t)base);
-    const uint32_t base_hi = __builtin_amdgcn_readfirstlane((uint32_t)(base >> 32));
-    void *bp = (void *)(uintptr_t)(((uint64_t)base_hi << 32) | base_lo);
-    const __amdgpu_buffer_rsrc_t rsrc =
-        __builtin_amdgcn_make_buffer_rsrc(bp, (short)0, (int)extent, 0x00020000);
-    // per lane: byte offset of each word within a row and the bits of
-    // inputs < N; a word past the row reads the last word (kVec: the last
-    // four), masked to 0
-    uint32_t off[SIDES][4], pad[SIDES][4];
-#pragma unroll
-    for (int side = 0; side < SIDES; ++side)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int gw = (side == 0 ? R : C) * kSuper + 4 * (lane & 1) + r;
-            const int left = a.N - gw * 32;
-            off[side][r] = kVec ? 4u * (uint32_t)min(gw - r, a.W - 4) + 4u * r
-                                : 4u * (uint32_t)min(gw, a.W - 1);
-            pad[side][r] = left >= 32 ? 0xffffffffu : left > 0 ? (1u << left) - 1u : 0u;
-        }
-    const uint32_t smp = (uint32_t)(lane >> 1);
-    const uint32_t step_bytes = 32u * S::kWaves * row_bytes;
-    auto batch_row = [&](int j0) {
-        return (32u * (uint32_t)(wave + S::kWaves * j0) + smp) * row_bytes;
+    const uint64_t p = ((uint64_t)uniform((uint32_t)(base >> 32)) << 32) | uniform((uint32_t)base);
+    w.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(uintptr_t)p, (short)0,
+                                               (int)uniform((uint32_t)w.samples * w.row_bytes),
+                                               0x00020000);
+    // The four column words' 16 bytes may reach into the next row, whose bits
+    // `pad` masks; the loads need no alignment.
+    auto pad = [&](int r) {
+        const int left = a.N - (col_word + r) * 32;
+        return left >= 32 ? -1 : left > 0 ? (int)((1u << left) - 1u) : 0;
     };
-    uint32_t raw[S::kBatch][SIDES][4];
-    load_batch<kVec, S::kBatch, SIDES>(raw, rsrc, off, batch_row(0), step_bytes);
-
-    // clear the counts, build the validity window
-    {
-        uint4 *z = (uint4 *)L.acc;
-        for (int e = tid; e < S::kTiles * S::kTileQuads / 2; e += S::kThreads)
-            z[e] = (uint4){0u, 0u, 0u, 0u};
-    }
-    fill_window(a, L, f, t_begin, t_end, tid);
+    w.pad = (v4i){pad(0), pad(1), pad(2), pad(3)};
+    w.at = (uint32_t)(64 * w.wave + w.lane) * w.row_bytes + 4u * (uint32_t)col_word;
+    w.at_rows = (uint32_t)(64 * w.wave + w.lane) * w.row_bytes + 4u * (uint32_t)row_word;
+    w.template load<0>(0);
+    for (int e = tid; e < U::kTiles * kTile; e += kThreads) L.acc[e] = 0;
+    fill_window<kThreads>(a, L.valid, f, t_begin, t_end, tid);
+#pragma unroll
+    for (int k = 0; k < U::kTiles; ++k) w.acc[k] = (v16f){0};
+#pragma unroll
+    for (int k = 0; k < U::kWords; ++k) w.op[k] = (v4i){0, 0, 0, 0};
     __syncthreads();   // counts cleared, validity window visible
-
-    constexpr uint64_t kEven = 0x5555555555555555ull;
-    constexpr int cs = SIDES - 1;   // side of the column blocks
-    uint32_t(*slot)[kSuper][32] = L.words[wave];
-    for (int j0 = 0; wave + S::kWaves * j0 < nsteps; j0 += S::kBatch) {
-        if (j0 > 0) load_batch<kVec, S::kBatch, SIDES>(raw, rsrc, off, batch_row(j0), step_bytes);
-#pragma unroll
-        for (int q = 0; q < S::kBatch; ++q) {
-            const int s = wave + S::kWaves * (j0 + q);
-            if (s >= nsteps) continue;
-            const uint32_t keep = 0u - ((L.valid[s] >> smp) & 1u);
-            uint32_t seen[SIDES];
-#pragma unroll
-            for (int side = 0; side < SIDES; ++side) {
-                seen[side] = 0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    raw[q][side][r] &= pad[side][r] & keep;
-                    seen[side] |= raw[q][side][r];
-                }
-            }
-            bool flagged = true;
-#pragma unroll
-            for (int side = 0; side < SIDES; ++side) flagged = flagged && __ballot(seen[side] != 0u) != 0;
-            if (!flagged) continue;
-            // bit b of blk[side]: block b of the side holds a flag
-            uint32_t blk[SIDES];
-#pragma unroll
-            for (int side = 0; side < SIDES; ++side) {
-                uint32_t bits = 0;
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const uint64_t m = __ballot(raw[q][side][r] != 0u);
-                    bits |= ((m & kEven) != 0 ? 1u : 0u) << r;
-                    bits |= ((m & ~kEven) != 0 ? 1u : 0u) << (4 + r);
-                }
-                blk[side] = __builtin_amdgcn_readfirstlane(bits);
-            }
-            // the step's words in this wave's slot, [side][block][sample]
-#pragma unroll
-            for (int side = 0; side < SIDES; ++side)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) slot[side][4 * (lane & 1) + r][smp] = raw[q][side][r];
-            // operands of the column side's flagged blocks; a row block's
-            // operand is the same (diagonal pair) or built when its row of
-            // tiles comes
-            v4i op[kSuper];
-#pragma unroll
-            for (int b = 0; b < kSuper; ++b)
-                if ((blk[cs] >> b) & 1u) op[b] = build_op(slot[cs][b], lane);
-            const v16i zero = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-            for (int bi = 0; bi < kSuper; ++bi) {
-                if (((blk[0] >> bi) & 1u) == 0u) continue;
-                const v4i row_op = kOff ? build_op(slot[0][bi], lane) : op[bi];
-#pragma unroll
-                for (int bj = kOff ? 0 : bi; bj < kSuper; ++bj) {
-                    if (((blk[cs] >> bj) & 1u) == 0u) continue;
-                    const int k = kOff ? bi * kSuper + bj
-                                       : bi * kSuper - bi * (bi - 1) / 2 + (bj - bi);
-                    add_tile<S::kPitch>(L.acc + k * S::kTileQuads, mfma(row_op, op[bj], zero),
-                                        lane);
-                }
-            }
-        }
-    }
+#pragma clang loop unroll(disable)
+    for (int b = 0; w.sample(b, 0) < w.samples; ++b) w.batch(b);
+    w.seen = uniform(w.seen);
+    w.template add_tiles<0>();
     __syncthreads();   // every wave's counts added
 
     // the nonzero counts into d
-    const int64_t P = (int64_t)a.N * (a.N + 1) / 2;
-    int32_t *dst = a.d + (int64_t)f * P;
-    for (int e = tid; e < S::kTiles * 256; e += S::kThreads) {
-        const int k = e >> 8, j = (e >> 3) & 31, Q = e & 7;
-        const uint64_t word = L.acc[k * S::kTileQuads + j * S::kPitch + Q];
+    int32_t *dst = a.d + (int64_t)f * a.N * (a.N + 1) / 2;
+#pragma clang loop unroll(disable)
+    for (int e = tid; e < U::kTiles * 256; e += kThreads) {
+        const int k = e >> 8, Q = (e >> 5) & 7, j = e & 31;
+        const uint64_t word = L.acc[k * kTile + j * kPitch + Q];
         if (word == 0u) continue;
-        int bi, bj;
-        if (kOff) {
-            bi = k >> 3;
-            bj = k & 7;
-        } else {
-            int kk = k;
-            bi = 0;
-            while (kk >= kSuper - bi) {
-                kk -= kSuper - bi;
-                ++bi;
-            }
-            bj = bi + kk;
-        }
-        const int gi = R * 256 + bi * 32 + 4 * Q, gj = C * 256 + bj * 32 + j;
+        const int gi = (row_word + U::row(k)) * 32 + 4 * Q;
+        const int gj = (col_word + U::col(k) - (kTri ? 0 : 2)) * 32 + j;
         if (gj >= a.N) continue;
+        int32_t *x = dst + tri(a.N, gi, gj);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int cnt = (int)((word >> (16 * r)) & 0xffffu);
-            if (cnt != 0 && gi + r <= gj) atomicAdd(dst + tri(a.N, gi + r, gj), cnt);
+            if (cnt != 0 && gi + r <= gj) atomicAdd(x, cnt);
+            x += a.N - 1 - gi - r;
         }
+    }
+}
+
+// Units of a channel: the triangles of its groups, then for every pair of
+// groups g < h the two halves of g's rows against h, row by row.
+__global__ __launch_bounds__(kThreads, 2) void gram_kernel(Args a) {
+    __shared__ __attribute__((aligned(16))) Lds L;
+    const int units = a.groups * a.groups;
+    const int64_t w = xcd_local(blockIdx.x, (int64_t)a.F * units * a.chunks);
+    const int u = (int)(w % units);
+    const int64_t rest = w / units;
+    const int chunk = (int)(rest % a.chunks);
+    const int f = (int)(rest / a.chunks);
+    const int t_begin = chunk * a.chunk_samples;
+    const int t_end = min(a.T, t_begin + a.chunk_samples);
+    if (u < a.groups) {
+        run_unit<true>(a, L, f, 4 * u, 4 * u, t_begin, t_end);
+    } else {
+        int rem = (u - a.groups) >> 1, g = 0;
+        while (rem >= a.groups - 1 - g) {
+            rem -= a.groups - 1 - g;
+            ++g;
+        }
+        run_unit<false>(a, L, f, 4 * g + 2 * ((u - a.groups) & 1), 4 * (g + 1 + rem), t_begin,
+                        t_end);
     }
 }
 

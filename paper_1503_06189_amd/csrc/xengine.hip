@@ -17,6 +17,7 @@
 #include "short_kernels.hpp"
 #include "xcorr_kernels.hpp"
 #include "flag_kernels.hpp"
+#include "flag_wide_kernels.hpp"
 #include "assemble_kernels.hpp"
 #include "shift_kernels.hpp"
 
@@ -510,11 +511,11 @@ xe_status launch_batch(xe_handle h, int slot, const SlotShape &sh, hipStream_t s
 
 namespace {
 
-// Work split of the flag Gram kernel: (channel, super-block pair, time
-// chunk), about one workgroup per compute unit (a diagonal pair's
-// workgroup holds 96 KB of LDS counts, an off-diagonal one 156 KB), chunks
-// of at least 64 steps (four per wave), and at most the kernel's
-// validity window of 32768 samples, whose counts also fit 16 bits.
+// Work split of the flag Gram kernels: (channel, unit of tiles or super-block
+// pair, time chunk), about one workgroup per compute unit: up to one of the
+// unit kernel's, whose chunks add the same counts again, at least one of the
+// wide kernel's.  Chunks have at least 64 32-sample steps, and at most the
+// kernels' validity window of 32,768 samples, whose counts also fit 16 bits.
 xe::flag::Args flag_args(const uint32_t *flags, const uint8_t *mask, int32_t N, int32_t F,
                          int32_t T, int32_t B, int32_t *d, int n_cu) {
     using namespace xe::flag;
@@ -528,10 +529,14 @@ xe::flag::Args flag_args(const uint32_t *flags, const uint8_t *mask, int32_t N, 
     a.B = B;
     a.W = (N + 31) / 32;
     a.nblk = (T + B - 1) / B;
+    a.groups = (N + 127) / 128;
     a.ns = (N + 255) / 256;
-    const int64_t units = (int64_t)F * (a.ns * (a.ns + 1) / 2);
+    const int64_t cu = std::max(n_cu, 1);
+    const bool wide = wide::use_wide(F, a.groups, n_cu);
+    const int64_t units =
+        (int64_t)F * (wide ? a.ns * (a.ns + 1) / 2 : (int64_t)a.groups * a.groups);
     const int64_t steps = (T + 31) / 32;
-    int64_t want = ((int64_t)std::max(n_cu, 1) + units - 1) / units;
+    int64_t want = wide ? (cu + units - 1) / units : cu / units;
     const int64_t most = std::max<int64_t>(1, steps / 64);
     want = std::min(std::max<int64_t>(want, 1), most);
     want = std::max(want, (steps + kWindow - 1) / kWindow);
@@ -731,23 +736,29 @@ xe_status xe_flag_accumulate(xe_handle h, const uint32_t *flags, const uint8_t *
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, XE_ERR_HIP, "hipSetDevice failed");
     xe::flag::Args a = flag_args(flags, loss_mask, N, F, T, eff_block(B, T), dcount, h->n_cu);
-    const int64_t diag_blocks = (int64_t)F * a.ns * a.chunks;
-    const int64_t off_blocks = (int64_t)F * (a.ns * (a.ns - 1) / 2) * a.chunks;
-    // 16-byte loads when a row is whole groups of four words, 16-byte aligned
-    const bool vec = a.W % 4 == 0 && aligned(flags, 16);
-    using xe::flag::Shape;
-    if (vec)
-        hipLaunchKernelGGL((xe::flag::gram_kernel<false, true>), dim3((unsigned)diag_blocks),
-                           dim3(Shape<false>::kThreads), 0, (hipStream_t)stream, a);
-    else
-        hipLaunchKernelGGL((xe::flag::gram_kernel<false, false>), dim3((unsigned)diag_blocks),
-                           dim3(Shape<false>::kThreads), 0, (hipStream_t)stream, a);
-    if (off_blocks > 0 && vec)
-        hipLaunchKernelGGL((xe::flag::gram_kernel<true, true>), dim3((unsigned)off_blocks),
-                           dim3(Shape<true>::kThreads), 0, (hipStream_t)stream, a);
-    else if (off_blocks > 0)
-        hipLaunchKernelGGL((xe::flag::gram_kernel<true, false>), dim3((unsigned)off_blocks),
-                           dim3(Shape<true>::kThreads), 0, (hipStream_t)stream, a);
+    if (xe::flag::wide::use_wide(F, a.groups, h->n_cu)) {
+        const unsigned diag = (unsigned)((int64_t)F * a.ns * a.chunks);
+        const unsigned off = (unsigned)((int64_t)F * (a.ns * (a.ns - 1) / 2) * a.chunks);
+        const dim3 threads(xe::flag::wide::Shape<false>::kThreads);
+        const dim3 off_threads(xe::flag::wide::Shape<true>::kThreads);
+        // 16-byte loads when a row is whole groups of four words, 16-byte aligned
+        // (more than two groups of inputs: off is not 0)
+        if (a.W % 4 == 0 && aligned(flags, 16)) {
+            hipLaunchKernelGGL((xe::flag::wide::gram_kernel<false, true>), dim3(diag), threads, 0,
+                               (hipStream_t)stream, a);
+            hipLaunchKernelGGL((xe::flag::wide::gram_kernel<true, true>), dim3(off), off_threads, 0,
+                               (hipStream_t)stream, a);
+        } else {
+            hipLaunchKernelGGL((xe::flag::wide::gram_kernel<false, false>), dim3(diag), threads, 0,
+                               (hipStream_t)stream, a);
+            hipLaunchKernelGGL((xe::flag::wide::gram_kernel<true, false>), dim3(off), off_threads,
+                               0, (hipStream_t)stream, a);
+        }
+    } else {
+        const int64_t blocks = (int64_t)F * a.groups * a.groups * a.chunks;
+        hipLaunchKernelGGL(xe::flag::gram_kernel, dim3((unsigned)blocks),
+                           dim3(xe::flag::kThreads), 0, (hipStream_t)stream, a);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "flag gram launch");
     return XE_OK;
