@@ -5,17 +5,19 @@
 // sequence number, writes zeros where a packet is missing, puts packets
 // that arrive out of order in their own place and ignores duplicates.
 // Here a batch of raw packets already in device memory (one host-to-device
-// copy of the receive ring) is placed by four launches:
-//   reset  owner[stream][slot] = "none", counters = 0;
+// copy of the receive ring) is placed by three launches:
+//   reset  owner[stream][slot] = "none", counters = 0, every place empty;
 //   claim  one thread per packet reads its header, checks stream, window
 //          and input count, and takes its (stream, slot) with an atomic
 //          minimum of its arrival index: the first arrival wins whatever
-//          order the threads run in, so duplicates are ignored;
+//          order the threads run in, so duplicates are ignored.  Who finds
+//          "none" there has filled a place that was empty: the counts of both
+//          come with the claims (a launch of their own, over the finished
+//          table, took 7 of a frame's 140 us);
 //   place  one workgroup per (stream, slot) copies the winner's 4 samples x
 //          8 bands of data into the frame and its footer flag words into
 //          the channel-major flag array, or, when no packet arrived, writes
-//          0 + 0i (byte 0x88), no flags and a lost block in the mask;
-//   count  places filled and left empty, from the owner table.
+//          0 + 0i (byte 0x88), no flags and a lost block in the mask.
 // Every output element is written, so buffers need no clearing between
 // frames.  Packet layout: 16-byte header (uint64 sequence number, uint32
 // stream id, uint32 input count N), data [4][8][N] bytes, footer
@@ -52,7 +54,8 @@ __global__ void reset_kernel(int32_t *owner, int64_t n, unsigned long long *stat
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += stride)
         owner[k] = kNone;
-    if (blockIdx.x == 0 && threadIdx.x < 6) stats[threadIdx.x] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x < 6)
+        stats[threadIdx.x] = threadIdx.x == 5 ? (unsigned long long)n : 0ull;
 }
 
 // Counters are summed per workgroup in LDS and added to the device counters
@@ -68,11 +71,12 @@ __device__ __forceinline__ void count_lds(unsigned int *c, bool pred) {
 __device__ __forceinline__ uint32_t le32(const uint8_t *p) { return *(const uint32_t *)p; }
 
 __global__ void claim_kernel(Args a) {
-    __shared__ unsigned int c[4];
-    if (threadIdx.x < 4) c[threadIdx.x] = 0u;
+    __shared__ unsigned int c[5];
+    if (threadIdx.x < 5) c[threadIdx.x] = 0u;
     __syncthreads();
     const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     bool in_window = false, out_window = false, unknown = false, malformed = false;
+    bool filled = false;
     if (p < a.n_packets) {
         const uint8_t *h = a.packets + p * a.pbytes;
         const uint64_t seq = (uint64_t)le32(h) | ((uint64_t)le32(h + 4) << 32);
@@ -86,35 +90,20 @@ __global__ void claim_kernel(Args a) {
             out_window = true;
         } else {
             in_window = true;
-            atomicMin(a.owner + s * a.slots + (int64_t)(seq - (uint64_t)a.seq0), (int32_t)p);
+            filled = atomicMin(a.owner + s * a.slots + (int64_t)(seq - (uint64_t)a.seq0),
+                               (int32_t)p) == kNone;
         }
     }
     count_lds(c + 0, in_window);
     count_lds(c + 1, out_window);
     count_lds(c + 2, unknown);
     count_lds(c + 3, malformed);
+    count_lds(c + 4, filled);
     __syncthreads();
-    if (threadIdx.x < 4 && c[threadIdx.x] != 0u)
+    if (threadIdx.x < 5 && c[threadIdx.x] != 0u)
         atomicAdd(a.stats + threadIdx.x, (unsigned long long)c[threadIdx.x]);
-}
-
-// places filled and left empty, from the owner table
-__global__ void count_kernel(const int32_t *owner, int64_t n, unsigned long long *stats) {
-    __shared__ unsigned int c[2];
-    if (threadIdx.x < 2) c[threadIdx.x] = 0u;
-    __syncthreads();
-    unsigned int filled = 0, empty = 0;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (int64_t k = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; k < n; k += stride) {
-        const bool f = owner[k] != kNone;
-        filled += f ? 1u : 0u;
-        empty += f ? 0u : 1u;
-    }
-    atomicAdd(c + 0, filled);
-    atomicAdd(c + 1, empty);
-    __syncthreads();
-    if (threadIdx.x < 2 && c[threadIdx.x] != 0u)
-        atomicAdd(stats + 4 + threadIdx.x, (unsigned long long)c[threadIdx.x]);
+    if (threadIdx.x == 5 && c[4] != 0u)
+        atomicAdd(a.stats + 5, 0ull - (unsigned long long)c[4]);
 }
 
 // kVec: 16-byte copies (N even, frame and packets 16-byte aligned)
