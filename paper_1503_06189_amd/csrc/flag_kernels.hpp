@@ -477,10 +477,70 @@ __global__ void apply_kernel(uint8_t *packed, const uint32_t *flags, int N, int 
 }
 
 // out[f][p] = vis / n_ij, n_ij = count_f - d_ii - d_jj + d_ij, in double
-// rounded once to float, 0 where n_ij == 0; n_out (optional) = n_ij.  One
-// thread per baseline; (i, j) from p by inverting the row starts
-// s(i) = i N - i (i - 1) / 2.
-__global__ void normalize_kernel(const int32_t *vis, const int64_t *count, const int32_t *d,
+// rounded once to float, 0 where n_ij == 0; n_out (optional) = n_ij.  A
+// workgroup takes rows i and N - 1 - i, N + 1 baselines, together; the
+// workgroups of a channel share its row pairs, with the channel's d_ii in LDS:
+// they lie a row apart in d.  Found from the baseline's number by a square
+// root, with d_jj fetched for every baseline, the rows took 355 us at 2048
+// inputs x 16 channels (671 MB), 30 at 512 x 32 and 16.4 at 256 x 64, and take
+// 197, 22 and 15.4.
+//
+// The quotients of a pair share one reciprocal: r = 1 / n and q = v r, both
+// rounded, and q + r (v - n q) with fused products is off by less than 2^-104
+// of v / n before its own rounding, while a quotient of integers below 2^31
+// and 2^50 that is no double lies at least 2^-103 of itself from any tie of two
+// doubles: the same doubles as division gives.
+constexpr int kNormThreads = 256;
+
+__device__ __forceinline__ float quotient(int v, double n, double r) {
+    const double x = (double)v, q = x * r;
+    return (float)__builtin_fma(__builtin_fma(-q, n, x), r, q);
+}
+
+__global__ __launch_bounds__(kNormThreads) void normalize_kernel(const int32_t *vis,
+                                                                 const int64_t *count,
+                                                                 const int32_t *d, float *out,
+                                                                 int32_t *n_out, int N,
+                                                                 int per_channel) {
+    extern __shared__ int32_t diag[];   // [N]
+    const int f = (int)(blockIdx.x / per_channel), b = (int)(blockIdx.x % per_channel);
+    const int64_t P = (int64_t)N * (N + 1) / 2;
+    const int32_t *df = d + f * P;
+    for (int i = threadIdx.x; i < N; i += kNormThreads) diag[i] = df[tri(N, i, i)];
+    __syncthreads();
+    const int64_t total = count[f];
+    const int2 *v = (const int2 *)vis + f * P;
+    float2 *o = (float2 *)out + f * P;
+    for (int i = b; 2 * i < N; i += per_channel) {
+        const int i2 = N - 1 - i, first = N - i;
+        const int len = i2 == i ? first : N + 1;
+        const int64_t s1 = tri(N, i, i), s2 = tri(N, i2, i2) - first;
+#pragma unroll 4
+        for (int k = threadIdx.x; k < len; k += kNormThreads) {
+            const bool one = k < first;
+            const int row = one ? i : i2, j = one ? i + k : i2 + k - first;
+            const int64_t p = (one ? s1 : s2) + k;
+            const int64_t n =
+                total - (int64_t)diag[row] - (int64_t)diag[j] + (int64_t)df[p];
+            const int2 x = v[p];
+            const double dn = (double)n, r = 1.0 / dn;
+            float2 y;
+            y.x = n == 0 ? 0.0f : quotient(x.x, dn, r);
+            y.y = n == 0 ? 0.0f : quotient(x.y, dn, r);
+            o[p] = y;
+            if (n_out) n_out[f * P + p] = (int32_t)n;
+        }
+    }
+}
+
+// The same for N <= kFewInputs, whose row pairs would leave half of a
+// workgroup's threads idle: one thread per baseline of all channels, (i, j)
+// from p by inverting the row starts s(i) = i N - i (i - 1) / 2.  64 inputs x
+// 1000 channels take 16 us so and 20 by row pairs, 100 x 500 18 and 19, 250 x 64
+// 15.8 and 13.7.
+constexpr int kFewInputs = 128;
+
+__global__ void normalize_few_kernel(const int32_t *vis, const int64_t *count, const int32_t *d,
                                  float *out, int32_t *n_out, int N, int F) {
     const int64_t P = (int64_t)N * (N + 1) / 2;
     const int64_t total = P * F;
@@ -499,8 +559,9 @@ __global__ void normalize_kernel(const int32_t *vis, const int64_t *count, const
                           (int64_t)df[p];
         const int2 v = *(const int2 *)(vis + 2 * e);
         float2 o;
-        o.x = n == 0 ? 0.0f : (float)((double)v.x / (double)n);
-        o.y = n == 0 ? 0.0f : (float)((double)v.y / (double)n);
+        const double dn = (double)n, r = 1.0 / dn;
+        o.x = n == 0 ? 0.0f : quotient(v.x, dn, r);
+        o.y = n == 0 ? 0.0f : quotient(v.y, dn, r);
         *(float2 *)(out + 2 * e) = o;
         if (n_out) n_out[e] = (int32_t)n;
     }

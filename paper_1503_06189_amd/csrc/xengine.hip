@@ -812,10 +812,18 @@ xe_status xe_normalize_flagged(xe_handle h, const int32_t *vis, const int64_t *c
     if (h->device == XE_DEVICE_NONE) return XE_ERR_NO_DEVICE;
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, XE_ERR_HIP, "hipSetDevice failed");
-    const int64_t total = P * F;
-    int64_t blocks = std::min<int64_t>((total + 255) / 256, 8192);
-    hipLaunchKernelGGL(xe::flag::normalize_kernel, dim3((unsigned)blocks), dim3(256), 0,
-                       (hipStream_t)stream, vis, count, dcount, out, n_out, N, F);
+    if (N <= xe::flag::kFewInputs) {
+        const int64_t blocks = std::min<int64_t>((P * F + 255) / 256, 8192);
+        hipLaunchKernelGGL(xe::flag::normalize_few_kernel, dim3((unsigned)blocks), dim3(256), 0,
+                           (hipStream_t)stream, vis, count, dcount, out, n_out, N, F);
+    } else {
+        // about 8 workgroups per compute unit, each with a row pair at least
+        const int64_t want = (8 * (int64_t)std::max(h->n_cu, 1) + F - 1) / F;
+        const int per = (int)std::min<int64_t>((N + 1) / 2, want);
+        hipLaunchKernelGGL(xe::flag::normalize_kernel, dim3((unsigned)((int64_t)F * per)),
+                           dim3(xe::flag::kNormThreads), (size_t)N * sizeof(int32_t),
+                           (hipStream_t)stream, vis, count, dcount, out, n_out, N, per);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "normalize flagged launch");
     return XE_OK;
