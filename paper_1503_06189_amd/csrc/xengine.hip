@@ -490,8 +490,10 @@ xe_status launch_batch(xe_handle h, int slot, const SlotShape &sh, hipStream_t s
         hipLaunchKernelGGL(xe::batch_kernel<true>,
                            dim3(std::min(h->n_cu, sh.n_small)), dim3(xe::kSmallThreads), 0, stream, bi,
                            small, sh.n_small, queues + 2, (int32_t *)h->workspace);
-    hipLaunchKernelGGL(xe::count_list_kernel, dim3((unsigned)sh.n_inst),
-                       dim3(64 * xe::kCountWaves), 0, stream, bi, sh.n_inst);
+    // two blocks per compute unit over all instances, at most 16 each
+    const int per_inst = std::max(1, std::min(16, 2 * h->n_cu / std::max(1, sh.n_inst)));
+    hipLaunchKernelGGL(xe::count_list_kernel, dim3((unsigned)sh.n_inst, (unsigned)per_inst),
+                       dim3(64 * xe::kCountWaves), 0, stream, bi);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(h, e, "batch launch");
     if (sh.n_merges > 0) {
