@@ -43,7 +43,13 @@
 // stage.  At the end waves 6 and 7 hand their sums to 4 and 5 through LDS,
 // which write them.
 //
-// Output: as in xcorr_kernels.hpp.
+// Output: as in xcorr_kernels.hpp, through range-checked accesses with every
+// address in 32 bits, so that no branch stands between a tile's loads and
+// stores.  With branches around them, a separate launch for the counts and
+// unaligned rows loaded byte by byte, 128 inputs x 256 channels x 512 samples
+// took 22.3 us and take 15.9, 256 x 256 x 64 23.5 and 20.1, 98 x 256 x 2048 67
+// and 35.  Short chunks are bound by the latency of their one pass: loads,
+// a few steps, the output read and written.
 #pragma once
 
 #include "xcorr_kernels.hpp"

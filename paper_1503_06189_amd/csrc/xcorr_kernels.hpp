@@ -245,9 +245,9 @@ __device__ __forceinline__ v4i sum_pattern(bool im, int lane) {
 }
 
 // Inline asm, because the four accumulators have to live in ordinary
-// registers: the tiles take every AGPR, and the compiler gives the builtin's
-// only those, at 8 register moves per instruction (a third of a step's issue
-// slots).  The compiler does not know the instruction's latency, so its
+// registers: in the halves geometry the tiles take every AGPR, and the compiler
+// gives the builtin's only those, at 8 register moves per instruction (a third
+// of a step's issue slots).  The compiler does not know the instruction's latency, so its
 // result must not be touched for 20 wait states: every use below follows it
 // by at least 8 of the 32-cycle tile instructions, or by a barrier.
 __device__ __forceinline__ void sum_mfma(v4i pat, v6i b, v4f &c) {
@@ -1311,7 +1311,10 @@ __device__ __forceinline__ void run_item(const CorrArgs &a, int f, int gid, int 
 // One frame: workgroup -> (channel, group, chunk), groups of a channel
 // and chunks of a (channel, group) numbered next to each other.
 template <bool kSmall>
-__global__ __launch_bounds__(kSmall ? kSmallThreads : kSuperThreads, kSmall ? 1 : 2) void corr_kernel(CorrArgs a) {
+constexpr int kThreadsOf = kSmall ? kSmallThreads : kSuperThreads;
+
+template <bool kSmall>
+__global__ __launch_bounds__(kThreadsOf<kSmall>, kSmall ? 1 : 2) void corr_kernel(CorrArgs a) {
     __shared__ __attribute__((aligned(16))) Lds<kSmall> lds;
     const int G = a.groups;
     const int64_t total = (int64_t)a.F * G * a.splits;
@@ -1351,10 +1354,9 @@ struct BatchItem {
 // instances' resident sums.  A batch has one list of items per geometry,
 // each drained by its own launch of this kernel.
 template <bool kSmall>
-__global__ __launch_bounds__(kSmall ? kSmallThreads : kSuperThreads, kSmall ? 1 : 2) void batch_kernel(const BatchInstance *inst,
-                                                            const BatchItem *items, int n_items,
-                                                            int *queue,
-                                                            int32_t *partials) {
+__global__ __launch_bounds__(kThreadsOf<kSmall>, kSmall ? 1 : 2) void batch_kernel(
+    const BatchInstance *inst, const BatchItem *items, int n_items, int *queue,
+    int32_t *partials) {
     __shared__ __attribute__((aligned(16))) Lds<kSmall> lds;
     __shared__ int s_item;
     for (;;) {
