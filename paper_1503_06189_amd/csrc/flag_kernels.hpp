@@ -227,7 +227,7 @@ struct Wave {
     uint32_t row0[kBatch], row1[kBatch];
     v4i op[U::kWords];
     v16f acc[U::kTiles];
-    uint32_t seen;                     // words that held a flag to count
+    uint32_t counted;                  // tiles with a count
 
     // sample of K-step q of batch b, lane 0 (ascending; a batch is one K-step
     // of every wave, kBatch times)
@@ -307,7 +307,10 @@ struct Wave {
     __device__ __forceinline__ void count(uint32_t flagged) {
         if constexpr (K < U::kTiles) {
             constexpr uint32_t both = 1u << U::row(K) | 1u << U::col(K);
-            if ((flagged & both) == both) acc[K] = mfma(op[U::row(K)], op[U::col(K)], acc[K]);
+            if ((flagged & both) == both) {
+                acc[K] = mfma(op[U::row(K)], op[U::col(K)], acc[K]);
+                counted |= 1u << K;
+            }
             count<K + 1>(flagged);
         }
     }
@@ -321,9 +324,7 @@ struct Wave {
             todo &= todo - 1;
             uint32_t w[U::kWords];
             take<0>(w, q);
-            const uint32_t flagged = uniform(operands<0>(w));
-            seen |= flagged;
-            count<0>(flagged);
+            count<0>(uniform(operands<0>(w)));
         }
     }
     // Adds the wave's counts into LDS: element v of a tile is at row
@@ -331,8 +332,7 @@ struct Wave {
     template <int K>
     __device__ __forceinline__ void add_tiles() {
         if constexpr (K < U::kTiles) {
-            constexpr uint32_t both = 1u << U::row(K) | 1u << U::col(K);
-            if ((seen & both) == both) {
+            if ((counted >> K) & 1u) {
                 uint64_t *t = L.acc + K * kTile + shuffled(lane & 31) * kPitch + (lane >> 5);
                 const bool odd = lane >= 32;   // rows 4 .. 7 of 8: in reverse
 #pragma unroll
@@ -360,7 +360,7 @@ __device__ __forceinline__ void run_unit(const Args &a, Lds &L, int f, int row_w
     w.lane = tid & 63;
     w.wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     w.samples = t_end - t_begin;
-    w.seen = 0;
+    w.counted = 0;
     // the chunk's rows of this channel's flags through a buffer resource
     // whose range ends at the chunk's last sample: dwords past it read 0
     // without a memory access
@@ -389,7 +389,7 @@ __device__ __forceinline__ void run_unit(const Args &a, Lds &L, int f, int row_w
     __syncthreads();   // counts cleared, validity window visible
 #pragma clang loop unroll(disable)
     for (int b = 0; w.sample(b, 0) < w.samples; ++b) w.batch(b);
-    w.seen = uniform(w.seen);
+    w.counted = uniform(w.counted);
     w.template add_tiles<0>();
     __syncthreads();   // every wave's counts added
 
