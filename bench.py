@@ -12,7 +12,9 @@ Prints ONE JSON line.  Fields beyond the common ones:
   roofline      the correlation call (correlation kernel + the merge of
                 its time chunks) against the int8 MFMA peak: the
                 algorithmic ops per call (8 per channel, upper-triangle
-                pair and sample) over its average duration, timed with HIP
+                pair and sample; chunks this long run on the 6-bit matrix
+                path, whose dense peak is twice that) over its average
+                duration, timed with HIP
                 events on the stream it runs on; traffic = HBM bytes per
                 call from the committed counter runs, when they were
                 taken on the current kernel source
@@ -101,7 +103,7 @@ def measured_traffic():
 
 def measured_execution():
     """Executed matrix-core work of corr_kernel from the committed SQ
-    counter runs, or None: executed int8 ops against the algorithmic ones,
+    counter runs, or None: executed ops against the algorithmic ones,
     and the fraction of the kernel's cycles the SIMDs' matrix cores were
     busy (SQ_VALU_MFMA_BUSY_CYCLES per SIMD over GRBM_GUI_ACTIVE per XCD),
     mean over the profiled dispatches and for the fastest one."""
@@ -110,8 +112,8 @@ def measured_execution():
     if not sq:
         return None
     return {
-        "executed_int8_ops": sq["executed_int8_ops"],
-        "algorithmic_int8_ops": sq["algorithmic_int8_ops"],
+        "executed_ops": sq["executed_ops"],
+        "algorithmic_ops": sq["algorithmic_ops"],
         "mfma_busy_frac_mean": sq["mfma_busy_frac_mean"],
         "mfma_busy_frac_best": sq["mfma_busy_frac_best"],
         "source": os.path.basename(PMC_FILE),
