@@ -247,11 +247,16 @@ __device__ __forceinline__ v4i sum_pattern(bool im, int lane) {
 // Inline asm, because the four accumulators have to live in ordinary
 // registers: in the halves geometry the tiles take every AGPR, and the compiler
 // gives the builtin's only those, at 8 register moves per instruction (a third
-// of a step's issue slots).  The compiler does not know the instruction's latency, so its
-// result must not be touched for 20 wait states: every use below follows it
-// by at least 8 of the 32-cycle tile instructions, or by a barrier.
+// of a step's issue slots).  The compiler keeps no distances around it:
+//   * a register that a vector instruction has just written may be read 2 wait
+//     states later at the earliest, as any of the three operands: the s_nop
+//     (with it, two of these may also follow each other on one accumulator);
+//   * its result must not be touched for 20 wait states: every use below
+//     follows it by at least 8 of the 32-cycle tile instructions, or by a
+//     barrier.
 __device__ __forceinline__ void sum_mfma(v4i pat, v6i b, v4f &c) {
-    asm volatile("v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:4 blgp:2"
+    asm volatile("s_nop 1\n\t"
+                 "v_mfma_f32_16x16x128_f8f6f4 %0, %1, %2, %0 cbsz:4 blgp:2"
                  : "+v"(c)
                  : "v"(pat), "v"(b));
 }
