@@ -61,18 +61,20 @@ XE_HD inline int use_short(int small, int steps) {
 }
 // longest chunk: 2^18 steps (8,388,608 samples)
 constexpr int kMaxStepsPerChunk = 1 << 18;
-// Chunk lengths are multiples of kDepth steps, and the byte offsets of a chunk
-// plus 4 * kDepth steps stay below 2^31.
+// Chunk lengths are multiples of kDepth steps.  A chunk of n steps is loaded
+// n + 3 kDepth steps far at most, lookahead included, and byte offsets within
+// that stay below 2^31.
 #ifndef XE_DEPTH
 #define XE_DEPTH 4
 #endif
 constexpr int kDepth = XE_DEPTH;
 
-// longest chunk (in steps) whose byte offsets, with 4 * kDepth steps of slack,
-// stay below 2^31 for F channels of N inputs
+// Longest chunk (in steps) for F channels of N inputs, kDepth steps at least:
+// these fit for every F * N that the ABI accepts (asserted with its check).
 inline int64_t max_steps_per_chunk(int64_t F, int64_t N) {
     int64_t m = (((int64_t)1 << 31) - 1) / (F * N * kStep) - 4 * kDepth;
     if (m > kMaxStepsPerChunk) m = kMaxStepsPerChunk;
+    if (m < kDepth) m = kDepth;
     return m - m % kDepth;
 }
 

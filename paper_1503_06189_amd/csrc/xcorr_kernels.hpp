@@ -300,8 +300,10 @@ __device__ __forceinline__ Chunk make_chunk(const CorrArgs &a, int f, int t_begi
     return c;
 }
 
-// The chunk from `skip` bytes on (whole rows plus a group's first input).
-// skip stays below 2^32, the lookahead past a chunk included.
+// The chunk from `skip` bytes on (whole rows plus a group's first input).  The
+// lookahead past a chunk may pass 2^32 where F * N is above 2^20 (halves
+// geometry, 20 loop steps): what wraps into the chunk reads bytes of it, which
+// the zero validity words of those steps discard.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const Chunk &ch, uint32_t skip) {
     uint64_t p = ch.base + skip;
     p = ((uint64_t)uniform((uint32_t)(p >> 32)) << 32) | uniform((uint32_t)p);

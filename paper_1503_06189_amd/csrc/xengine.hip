@@ -103,9 +103,10 @@ xe_status check_shape(xe_handle h, int32_t N, int32_t F, int32_t T, int32_t B) {
     int64_t P = (int64_t)N * (N + 1) / 2;
     if ((int64_t)F * P * 2 > ((int64_t)1 << 40)) return fail(h, XE_ERR_ARG, "F*P too large");
     if ((int64_t)T * F * N > ((int64_t)1 << 40)) return fail(h, XE_ERR_ARG, "frame too large");
-    // a chunk with its lookahead must stay addressable with 31-bit offsets
-    static_assert((int64_t)XE_MAX_FN * xe::kStep * (2 * xe::kDepth + 2) < ((int64_t)1 << 31),
-                  "XE_MAX_FN too large for the prefetch depth");
+    // the shortest chunk of max_steps_per_chunk, with its lookahead, must stay
+    // addressable with 31-bit offsets
+    static_assert((int64_t)XE_MAX_FN * xe::kStep * 4 * xe::kDepth <= (int64_t)1 << 31,
+                  "XE_MAX_FN too large for the lookahead");
     if ((int64_t)F * N > XE_MAX_FN) return fail(h, XE_ERR_ARG, "F*N exceeds XE_MAX_FN");
     return XE_OK;
 }
