@@ -7,7 +7,7 @@
 // sparse, these loads take longer than the counting: this kernel loads 256
 // inputs' words at a time and a fifth as often, and adds every step's counts
 // into LDS, which is cheap while few blocks are flagged.  Where the line lies:
-// see use_wide() below.
+// see use_wide_flags() in plan.hpp.
 //
 // A workgroup takes one channel, one pair of 256-input super blocks (R <= C)
 // and one chunk of time; its waves take the chunk's 32-sample steps in turn
@@ -34,24 +34,6 @@ namespace wide {
 typedef int v16i __attribute__((ext_vector_type(16)));
 
 constexpr int kSuper = 8;           // 32-input blocks per super block
-
-// Measured, unit kernel against this one, us per call: bursts of 32 over
-// 0.05 - 0.1% of the points, then 0.05% or 1 - 5% scattered:
-//   256 inputs, 64 channels,  16,384 samples:  14 | 12,   42 |  135
-//   512 inputs, 32 channels,   8,192 samples:  18 | 21,   50 |  448
-//   512 inputs, 64 channels,   4,096 samples:  22 | 17
-//   640 inputs, 25 channels,  16,384 samples:  42 | 30
-//   768 inputs, 21 channels,  16,384 samples:  50 | 26,  122 |  824
-//   1024 inputs, 2 channels,   8,192 samples:  12 | 25
-//   1024 inputs, 4 channels,  16,384 samples:  22 | 19
-// How dense the flags are is not known before they are read, so sparse flags
-// decide, which are the method's case: up to two workgroups per compute unit
-// the units win, from rows of more than 64 bytes only where they fill less
-// than the GPU.
-inline bool use_wide(int64_t F, int groups, int n_cu) {
-    const int64_t units = F * groups * groups;
-    return groups > 2 && units > (groups <= 4 ? 2 * (int64_t)n_cu : n_cu / 2);
-}
 
 // A diagonal pair (R == C) has 36 tiles of 32 x 32 counts (blocks bi <= bj)
 // and runs 16 waves; an off-diagonal pair (R < C) has 64 and runs 8 waves,

@@ -535,7 +535,7 @@ xe::flag::Args flag_args(const uint32_t *flags, const uint8_t *mask, int32_t N, 
     a.groups = (N + 127) / 128;
     a.ns = (N + 255) / 256;
     const int64_t cu = std::max(n_cu, 1);
-    const bool wide = wide::use_wide(F, a.groups, n_cu);
+    const bool wide = xe::use_wide_flags(F, a.groups, n_cu);
     const int64_t units =
         (int64_t)F * (wide ? a.ns * (a.ns + 1) / 2 : (int64_t)a.groups * a.groups);
     const int64_t steps = (T + 31) / 32;
@@ -739,24 +739,25 @@ xe_status xe_flag_accumulate(xe_handle h, const uint32_t *flags, const uint8_t *
     DeviceGuard g(h->device);
     if (!g.ok) return fail(h, XE_ERR_HIP, "hipSetDevice failed");
     xe::flag::Args a = flag_args(flags, loss_mask, N, F, T, eff_block(B, T), dcount, h->n_cu);
-    if (xe::flag::wide::use_wide(F, a.groups, h->n_cu)) {
+    if (xe::use_wide_flags(F, a.groups, h->n_cu)) {
         const unsigned diag = (unsigned)((int64_t)F * a.ns * a.chunks);
         const unsigned off = (unsigned)((int64_t)F * (a.ns * (a.ns - 1) / 2) * a.chunks);
         const dim3 threads(xe::flag::wide::Shape<false>::kThreads);
         const dim3 off_threads(xe::flag::wide::Shape<true>::kThreads);
         // 16-byte loads when a row is whole groups of four words, 16-byte aligned
-        // (more than two groups of inputs: off is not 0)
-        if (a.W % 4 == 0 && aligned(flags, 16)) {
+        const bool vec = a.W % 4 == 0 && aligned(flags, 16);
+        if (vec)
             hipLaunchKernelGGL((xe::flag::wide::gram_kernel<false, true>), dim3(diag), threads, 0,
                                (hipStream_t)stream, a);
-            hipLaunchKernelGGL((xe::flag::wide::gram_kernel<true, true>), dim3(off), off_threads, 0,
-                               (hipStream_t)stream, a);
-        } else {
+        else
             hipLaunchKernelGGL((xe::flag::wide::gram_kernel<false, false>), dim3(diag), threads, 0,
                                (hipStream_t)stream, a);
+        if (off > 0 && vec)
+            hipLaunchKernelGGL((xe::flag::wide::gram_kernel<true, true>), dim3(off), off_threads, 0,
+                               (hipStream_t)stream, a);
+        else if (off > 0)
             hipLaunchKernelGGL((xe::flag::wide::gram_kernel<true, false>), dim3(off), off_threads,
                                0, (hipStream_t)stream, a);
-        }
     } else {
         const int64_t blocks = (int64_t)F * a.groups * a.groups * a.chunks;
         hipLaunchKernelGGL(xe::flag::gram_kernel, dim3((unsigned)blocks),
