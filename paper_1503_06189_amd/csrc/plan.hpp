@@ -42,22 +42,41 @@ constexpr int kSmallWaves = 4, kSmallThreads = 64 * kSmallWaves;   // halves geo
 // Workspace of one tile group and time chunk, in int32 values: at least the
 // chunk's copy of the group's share of the output.
 constexpr int64_t kGroupPartial = 81920;
-// Chunks of at most this many 32-sample steps run on the int8 kernel
-// (short_kernels.hpp), longer ones on the 6-bit kernels (xcorr_kernels.hpp),
-// which pay more per workgroup and less per sample.  Measured, accumulating
-// unchunked frames, int8 against 6-bit, us per call:
+// Short time chunks run on the int8 kernel (short_kernels.hpp), longer ones on
+// the 6-bit kernels (xcorr_kernels.hpp), which pay more per workgroup and less
+// per sample.  Measured, accumulating unchunked frames, int8 | 6-bit, us per
+// call:
 //   128 inputs, 256 channels:  512 samples 15.9 | 26.1, 1536: 28.2 | 33.7,
 //                              2048: 34 | 36, 4096: 66 | 49
-//   256 inputs, 256 channels:  256 samples 26.2 | 31.1, 512: 32.3 | 35.5,
-//                              768: 38 | 40, 1024: 45 | 45, 2048: 78 | 61
+//   256 inputs, 256 channels:  512 samples 32.3 | 35.5, 800: 57 | 60,
+//                              1024: 60 | 62, 1280: 67 | 66, 2048: 91 | 80
+//   512 inputs, 294 channels:  800: 281 | 326, 1024: 312 | 333, 1536: 413 | 383
+//   768 inputs, 130 channels:  800: 277 | 291, 1024: 300 | 304, 1280: 345 | 330
 //   2048 inputs, 16 channels:  256 samples 86 | 97, 768: 134 | 138,
 //                              2048: 283 | 231
+//   1024 inputs, 32 channels:  768: 96 | 96, 800: 104 | 100, 1024: 110 | 105
+// Padding of the super geometry (inputs past N up to whole super-blocks) costs
+// the 6-bit kernel more:
+//   132 inputs, 1177 channels: 800: 186 | 233, 1280: 245 | 273, 2048: 360 | 360
+//   260 inputs, 294 channels:  800: 185 | 246, 1280: 238 | 282, 2048: 343 | 340
+//   516 inputs, 130 channels:  800: 187 | 219, 1280: 242 | 257, 1536: 288 | 283
+//   640 inputs, 130 channels:  800: 227 | 253, 1280: 294 | 299, 1536: 335 | 331
+// Rows that are not 4-byte aligned cost the int8 kernel more, in its
+// off-diagonal groups above all:
+//   250 inputs, 1177 channels: 800: 300 | 332, 1024: 325 | 341, 1280: 368 | 365
+//   257 inputs, 294 channels:  768: 248 | 244, 800: 274 | 252
+//   601 inputs, 130 channels:  768: 272 | 270, 800: 296 | 258
 // kShortSteps is also the most validity words that the int8 kernel keeps (one
 // per lane).
-constexpr int kShortSteps = 64;        // halves geometry
-constexpr int kShortSuperSteps = 24;   // super geometry
-XE_HD inline int use_short(int small, int steps) {
-    return steps <= (small ? kShortSteps : kShortSuperSteps);
+constexpr int kShortSteps = 64;         // halves geometry
+constexpr int kShortSuperSteps = 24;    // super geometry: many inputs, unaligned rows
+constexpr int kShortFewSteps = 32;      // up to three super-blocks
+constexpr int kShortPaddedSteps = 40;   // of which padding takes a quarter
+XE_HD inline int short_steps(int small, int N, int aligned) {
+    const int edge = kSuper * kBlk, ns = (N + edge - 1) / edge;
+    if (small) return kShortSteps;
+    if (ns > 3 || (ns > 1 && !aligned)) return kShortSuperSteps;
+    return 4 * N <= 3 * ns * edge ? kShortPaddedSteps : kShortFewSteps;
 }
 // longest chunk: 2^18 steps (8,388,608 samples)
 constexpr int kMaxStepsPerChunk = 1 << 18;

@@ -215,14 +215,14 @@ xe_status launch_corr(xe_handle h, const Scratch &ws, const uint8_t *packed, con
     if (p.workgroups > 0x7fffffff) return fail(h, XE_ERR_ARG, "too many workgroups");
     const bool small = xe::use_halves(halves, p.blocks);
     dim3 grid((unsigned)p.workgroups), block(small ? xe::kSmallThreads : xe::kSuperThreads);
+    const bool al = aligned(packed, 4) && N % 4 == 0;
     // (a frame of less than 4 bytes: the int8 kernel's unaligned loads need 4)
     const bool brief =
-        xe::use_short(small, p.steps_per_split) && (int64_t)T * F * N >= 4;
+        p.steps_per_split <= xe::short_steps(small, N, al) && (int64_t)T * F * N >= 4;
     // The valid-sample counts of a chunked frame come from extra blocks of the
     // merge launch; an unchunked one's workgroups count what they integrate.
     if (p.splits > 1) a.count = nullptr;
     if (brief) {
-        const bool al = aligned(packed, 4) && N % 4 == 0;
         const dim3 threads(xe::brief::kThreads);
         if (al && overwrite)
             hipLaunchKernelGGL((xe::brief::corr_kernel<true, true>), grid, threads, 0, stream, a,

@@ -35,3 +35,17 @@ WIDE = [(16, 400, 0), (128, 4000, 0), (129, 128, 0), (129, 129, 1), (256, 64, 0)
 def test_flag_counts(tmp_path):
     got = evaluate(tmp_path, [f"use_wide_flags({F}, {-(-N // 128)}, 256)" for N, F, _ in WIDE])
     assert got == [w for _, _, w in WIDE]
+
+
+# (halves geometry, inputs, 4-byte aligned rows, longest chunk of the int8
+# kernel in steps); frames of 25 to 40 steps were slower on the 6-bit kernel
+SHORT = [(1, 64, 1, 64), (1, 127, 0, 64), (0, 100, 1, 40), (0, 132, 1, 40), (0, 130, 0, 40),
+         (0, 192, 1, 40), (0, 193, 0, 32), (0, 250, 0, 32), (0, 256, 1, 32), (0, 257, 0, 24),
+         (0, 260, 1, 40), (0, 384, 1, 40), (0, 388, 1, 32), (0, 512, 1, 32), (0, 512, 0, 24),
+         (0, 576, 1, 40), (0, 580, 1, 32), (0, 768, 1, 32), (0, 772, 1, 24), (0, 1024, 1, 24),
+         (0, 2048, 1, 24)]
+
+
+def test_short_chunks(tmp_path):
+    got = evaluate(tmp_path, [f"short_steps({s}, {N}, {a})" for s, N, a, _ in SHORT])
+    assert got == [n for _, _, _, n in SHORT]
