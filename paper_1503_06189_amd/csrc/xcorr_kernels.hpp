@@ -271,9 +271,9 @@ __device__ __forceinline__ int units(float x) { return (int)(x * 64.0f); }
 // through a buffer resource whose range ends with the last dword of the
 // chunk's last row, so every dword is checked by the hardware and reads 0
 // past it.  All members are wave-uniform.
-// Inputs past N (lanes of the last group) read the next channel's bytes or 0;
-// their products are never stored.  Only the frame's end may cut a dword off
-// (N % 4 != 0): see Tail.
+// 16-byte pieces past N are not loaded; inputs past N in the last piece read the
+// next channel's bytes or 0, and their products are never stored.  Only the
+// frame's end may cut a dword off (N % 4 != 0): see Tail.
 struct Chunk {
     uint64_t base;   // address of (t_begin, f, input 0)
     uint32_t row;    // F * N: bytes between consecutive samples
@@ -319,14 +319,18 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t chunk_rsrc(const Chunk &ch, ui
 // costs an address cycle per quad of lanes: 23 bytes per ns and CU against 72
 // with 16-byte loads, less than the matrix cores take in.  Rows 16..31 lie
 // 128 bytes further, on the other 32 banks.  The loads may have any byte
-// alignment.
+// alignment.  Pieces of inputs past N, `inputs` from the group's first, have an
+// offset out of range: loaded as bytes of the next channels they cost frames of
+// 132 to 388 inputs 2% (260 inputs, 300 channels, 1,200 samples: 284 | 277 us).
 constexpr uint32_t kNowhere = 0x80000000u;   // an offset out of every range
 constexpr int kRawBytes = 32 * kGroupInputs + 128;
 
-__device__ __forceinline__ void raw_offsets(uint32_t (&voff)[4], uint32_t row, int lane) {
+__device__ __forceinline__ void raw_offsets(uint32_t (&voff)[4], uint32_t row, int inputs,
+                                            int lane) {
+    const uint32_t col = 16 * (lane & 7) < inputs ? 16 * (uint32_t)(lane & 7) : kNowhere;
 #pragma unroll
     for (int k = 0; k < 4; ++k)
-        voff[k] = (uint32_t)(8 * k + (lane >> 3)) * row + 16 * (uint32_t)(lane & 7);
+        voff[k] = (uint32_t)(8 * k + (lane >> 3)) * row + col;
 }
 
 template <int kFrom, int kTo>
@@ -992,7 +996,7 @@ __device__ __forceinline__ void run_super(const CorrArgs &a, const Group &g, int
         w.cache = 0;
         w.pat_re = sum_pattern(false, w.lane);
         w.pat_im = sum_pattern(true, w.lane);
-        raw_offsets(w.voff, ch.row, w.lane);
+        raw_offsets(w.voff, ch.row, a.N - w.in0, w.lane);
         load_raw<W::kFrom, W::kTo>(w.rows(0), w.voff, w.in[0]);
         if constexpr (W::kSets == 2) load_raw<W::kFrom, W::kTo>(w.rows(1), w.voff, w.in[1]);
         if (threadIdx.x == 0) lds.valid = 0;
@@ -1211,10 +1215,7 @@ __device__ __forceinline__ void run_small(const CorrArgs &a, const Group &g, int
         w.pat_re = sum_pattern(false, w.lane);
         w.pat_im = sum_pattern(true, w.lane);
         w.wave = wave;
-        raw_offsets(w.voff, ch.row, w.lane);
-        // lanes whose inputs lie past N read nothing
-        if (w.in0 + 16 * (w.lane & 7) >= a.N)
-            for (int k = 0; k < 4; ++k) w.voff[k] = kNowhere;
+        raw_offsets(w.voff, ch.row, a.N - w.in0, w.lane);
 #pragma unroll
         for (int k = 0; k < 2; ++k)
 #pragma unroll
