@@ -413,7 +413,6 @@ class StreamServer:
             s.waiting.append(fr)
 
     def _admit(self) -> None:
-        torch = self.torch
         self._take_arrivals()
         # slices of the oldest frame first, across streams, while slots last
         while True:
@@ -422,44 +421,63 @@ class StreamServer:
             if not head:
                 return
             _, sid = min(head)
-            s = self.streams[sid]
-            fr = s.waiting[0]
-            cfg = s.cfg
-            if fr.packed.is_cuda:
-                # already in HBM: the whole frame as one slice, nothing to copy
-                s.waiting.popleft()
-                fr.slices = fr.copied = 1
-                s.pending.append(_Slice(fr, 0, cfg.T, fr.packed, fr.mask, None))
-                continue
-            k = self.pool.take()
-            if k < 0:
-                self.admission_waits += 1
+            if not self._admit_slice(self.streams[sid]):
                 return          # no slot: wait for a batch to finish
-            j = fr.copied
-            t0 = j * s.slice_samples
-            t1 = min(cfg.T, t0 + s.slice_samples)
-            dp = self.pool.packed(k, (t1 - t0, cfg.F, cfg.N))
-            dm = None
-            if fr.mask is not None:
-                b0, b1 = t0 // cfg.B, -(-t1 // cfg.B)
-                hm = self.pool.mask(k, (cfg.F, b1 - b0), host=True)
-                hm.copy_(fr.mask[:, b0:b1])     # host to pinned host, a few KB
-                dm = self.pool.mask(k, (cfg.F, b1 - b0))
-            with torch.cuda.stream(self.copy_stream):
-                if j == 0:
-                    fr.ev_copy_start = torch.cuda.Event(enable_timing=True)
-                    fr.ev_copy_start.record(self.copy_stream)
-                    fr.t_copy_issue = time.perf_counter()
-                dp.copy_(fr.packed[t0:t1], non_blocking=True)
-                if dm is not None:
-                    dm.copy_(hm, non_blocking=True)
-                ev = torch.cuda.Event(enable_timing=True)
-                ev.record(self.copy_stream)
-            fr.copied += 1
-            if fr.copied == fr.slices:
-                fr.ev_copied = ev
-                s.waiting.popleft()
-            s.pending.append(_Slice(fr, t0, t1, dp, dm, ev, k))
+
+    def _admit_slice(self, s: _Stream) -> bool:
+        """Issue the copy of the next slice of the stream's oldest waiting
+        frame; False if there is no slot for it."""
+        torch = self.torch
+        fr = s.waiting[0]
+        cfg = s.cfg
+        if fr.packed.is_cuda:
+            # already in HBM: the whole frame as one slice, nothing to copy
+            s.waiting.popleft()
+            fr.slices = fr.copied = 1
+            s.pending.append(_Slice(fr, 0, cfg.T, fr.packed, fr.mask, None))
+            return True
+        k = self.pool.take()
+        if k < 0:
+            self.admission_waits += 1
+            return False
+        j = fr.copied
+        t0 = j * s.slice_samples
+        t1 = min(cfg.T, t0 + s.slice_samples)
+        dp = self.pool.packed(k, (t1 - t0, cfg.F, cfg.N))
+        dm = None
+        if fr.mask is not None:
+            b0, b1 = t0 // cfg.B, -(-t1 // cfg.B)
+            hm = self.pool.mask(k, (cfg.F, b1 - b0), host=True)
+            hm.copy_(fr.mask[:, b0:b1])     # host to pinned host, a few KB
+            dm = self.pool.mask(k, (cfg.F, b1 - b0))
+        with torch.cuda.stream(self.copy_stream):
+            if j == 0:
+                fr.ev_copy_start = torch.cuda.Event(enable_timing=True)
+                fr.ev_copy_start.record(self.copy_stream)
+                fr.t_copy_issue = time.perf_counter()
+            dp.copy_(fr.packed[t0:t1], non_blocking=True)
+            if dm is not None:
+                dm.copy_(hm, non_blocking=True)
+            ev = torch.cuda.Event(enable_timing=True)
+            ev.record(self.copy_stream)
+        fr.copied += 1
+        if fr.copied == fr.slices:
+            fr.ev_copied = ev
+            s.waiting.popleft()
+        s.pending.append(_Slice(fr, t0, t1, dp, dm, ev, k))
+        return True
+
+    def gather(self) -> None:
+        """Admit one slice of every stream that has frames and none admitted,
+        as far as slots last, and wait until these have landed: the next
+        launch takes a slice of each."""
+        self._take_arrivals()
+        for s in self.streams.values():
+            if s.waiting and not s.pending and not self._admit_slice(s):
+                break
+        for s in self.streams.values():
+            if s.pending and s.pending[0].ev_copied is not None:
+                s.pending[0].ev_copied.synchronize()
 
     def _launch(self) -> bool:
         torch = self.torch
@@ -803,6 +821,11 @@ def run_load(specs, frames_per_stream: Optional[int] = None, integrations: int =
     """Offer each stream's frames with Poisson arrivals at ``speed`` times
     its rate (``speed`` = inf: all at once) and serve them.
 
+    All at once means that every frame has been handed over, and a slice of
+    every stream has landed as far as slots last, before the first launch.
+    Otherwise frames would share a launch only where copies overtake the
+    launches, which takes launches longer than a copy.
+
     Each stream sends ``frames_per_stream`` frames (default: ``integrations``
     whole integrations; with ``duration``: as many as its rate offers in that
     many seconds, at the arrival times of a Poisson process given that
@@ -874,6 +897,9 @@ def run_load(specs, frames_per_stream: Optional[int] = None, integrations: int =
     t_start = time.perf_counter()
     try:
         prod.start()
+        if not np.isfinite(speed):
+            prod.join()
+            server.gather()
         server.serve(stop)
         prod.join()
     finally:
