@@ -5,18 +5,20 @@ A batch's work list cuts every (instance, channel, tile group) into time
 chunks; short chunks balance the persistent grid but cost a partial-sum
 round trip through HBM each, long chunks leave compute units idle at the
 tail.  Instances with N <= 128 run either as padded 256-input super-blocks
-or in the halves geometry (the 10 tiles of a 4-block triangle over pairs of
-32-sample steps).  The tuner times every feasible (geometry, chunk length)
+or in the halves geometry (the 10 tiles of a 4-block triangle, each wave over
+its own samples).  The tuner times every feasible (geometry, chunk length)
 candidate on scratch accumulators of the batch's own shapes (the caller's
 sums are never touched), keeps the fastest, and caches the choice in a
 JSON file keyed by the device architecture and the batch's shape
-signature.
+signature.  An entry holds for the kernels it was timed on: it carries a digest
+of the library, and is timed anew once that changes.
 
 Cache file: ``$XE_TUNE_CACHE`` if set, else ``~/.cache/xengine/tune.json``.
 """
 
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
@@ -28,8 +30,9 @@ from . import xengine
 
 _lock = threading.Lock()
 
-#: cache entries written by this version (older entries carry no geometry)
-CACHE_VERSION = 2
+#: cache entries written by this version (older entries carry no geometry, or
+#: no digest of the library)
+CACHE_VERSION = 3
 
 
 @dataclass(frozen=True)
@@ -50,6 +53,27 @@ def signature(shapes: Sequence[Tuple[int, int, int, int]]) -> str:
     """Order-free digest of the instances' (N, F, T, B)."""
     text = ";".join(f"{n},{f},{t},{b}" for n, f, t, b in sorted(shapes))
     return hashlib.sha256(text.encode()).hexdigest()[:20]
+
+
+@functools.lru_cache(maxsize=None)
+def _digest(path: str, mtime_ns: int, size: int) -> str:
+    h = hashlib.sha256()
+    with open(path, "rb") as f:
+        for block in iter(lambda: f.read(1 << 20), b""):
+            h.update(block)
+    return h.hexdigest()[:20]
+
+
+def library_digest() -> str:
+    """Digest of the built library, whose kernels the timings hold for."""
+    st = os.stat(xengine.LIB_PATH)
+    return _digest(xengine.LIB_PATH, st.st_mtime_ns, st.st_size)
+
+
+def _current(entry: Optional[dict]) -> bool:
+    """Whether a cache entry was timed by this version on this library."""
+    return (entry is not None and entry.get("version") == CACHE_VERSION and
+            entry.get("library") == library_digest())
 
 
 def _arch(device: int) -> str:
@@ -111,7 +135,7 @@ def lookup(items: Sequence[Tuple], path: Optional[str] = None) -> Optional[dict]
     if not items:
         return None
     hit = load_cache(path).get(_key(items)[0])
-    return hit if hit is not None and hit.get("version") == CACHE_VERSION else None
+    return hit if _current(hit) else None
 
 
 def best_by_geometry(entry: dict) -> Dict[str, float]:
@@ -134,7 +158,7 @@ def tune(items: Sequence[Tuple], handle: Optional[xengine.Handle] = None,
     key, shapes = _key(items)
     if use_cache:
         hit = load_cache(path).get(key)
-        if hit is not None and hit.get("version") == CACHE_VERSION:
+        if _current(hit):
             return Choice(int(hit["chunk_steps"]), str(hit["geometry"]))
     n_cu = torch.cuda.get_device_properties(dev.index).multi_processor_count
     h = handle or xengine.default_handle(dev.index)
@@ -160,7 +184,7 @@ def tune(items: Sequence[Tuple], handle: Optional[xengine.Handle] = None,
                 plan.release()
     del scratch
     geom, cs = min(timings, key=timings.get)
-    _store(key, {"version": CACHE_VERSION, "chunk_steps": cs, "geometry": geom,
+    _store(key, {"version": CACHE_VERSION, "library": library_digest(), "chunk_steps": cs, "geometry": geom,
                  "ms": timings[(geom, cs)],
                  "timings_ms": {f"{g}/{c}": round(v, 5) for (g, c), v in timings.items()},
                  "instances": len(shapes)}, path)
