@@ -12,10 +12,10 @@ Prints ONE JSON line.  Fields beyond the common ones:
   roofline      the correlation call (correlation kernel + the merge of
                 its time chunks) against the int8 MFMA peak: the
                 algorithmic ops per call (8 per channel, upper-triangle
-                pair and sample; chunks this long run on the 6-bit matrix
-                path, whose dense peak is twice that) over its average
-                duration, timed with HIP
-                events on the stream it runs on; traffic = HBM bytes per
+                pair and sample) over its average duration, timed with HIP
+                events on the stream it runs on; path = the matrix
+                instructions that chunks of this length run on, their dense
+                peak and the fraction of it; traffic = HBM bytes per
                 call from the committed counter runs, when they were
                 taken on the current kernel source
   batched       128 uneven single-channel instances (N 64..1024, 1024 to
@@ -56,6 +56,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 MFMA_INT8_PEAK_TOPS = 5000.0   # MI355X dense int8, tera-ops/s
+MFMA_6BIT_PEAK_TOPS = 10000.0  # and in the 6-bit formats, which long chunks run on
 HBM_PEAK_GBPS = 8000.0
 PMC_FILE = os.path.join(ROOT, "profiles", "corr_pathfinder_n256_f64_t16384_pmc.json")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_1503_06189_amd", "csrc", f)
@@ -768,6 +769,9 @@ def main():
             "peak": MFMA_INT8_PEAK_TOPS,
             "unit": "TOPS",
             "frac": round(achieved_tops / MFMA_INT8_PEAK_TOPS, 4),
+            "path": {"operands": "6-bit (E2M3), exact integer sums in float32",
+                     "peak": MFMA_6BIT_PEAK_TOPS,
+                     "frac": round(achieved_tops / MFMA_6BIT_PEAK_TOPS, 4)},
             "traffic": measured_traffic(),
             "executed": measured_execution(),
         },

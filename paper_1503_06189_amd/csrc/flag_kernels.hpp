@@ -31,19 +31,20 @@
 //      words both hold a flag.  The counts stay in registers: float32 is
 //      exact up to 2^24, a chunk has at most 32,768 samples;
 //   4. at the chunk's end the waves' counts are added in LDS (16 bits each,
-//      four per word), and the nonzero ones into d: a unit's only chunk owns
-//      its counts and adds them plainly, several chunks use integer atomics,
-//      whose order does not matter.
-// What bounds it: sparse flags cost their loads, 33.6 MB for 256 inputs, 64
-// channels and 16,384 samples (zeroing and counting 17.6 us with bursts over
-// 0.1% of the points); scattered flags (5%) the vector instructions of the
-// transposes: 512 inputs, 32 channels, 8,192 samples take 53 us, where adding
-// the counts of every 32-sample step into LDS on their own took 449 us, the
-// LDS atomics' rate.  The units are this small, although their words are
-// loaded and transposed 2.5 times, because a channel's counts then come from
-// one chunk: with 36 tiles to a workgroup and four chunks to a channel the
-// global atomics took 34 of 59 us (256 dense inputs).  Many inputs: see
-// flag_wide_kernels.hpp.
+//      four per word), and the nonzero ones into d with integer atomics: other
+//      chunks, and calls on other streams, may add to the same counts, and the
+//      order does not matter.
+// What bounds it: 256 inputs, 64 channels and 16,384 samples (33.6 MB) with
+// bursts over 0.1% of the points take 14.7 us and 8.7 without a flag, the time
+// of a launch; without the LDS additions they take 12.4, without the flagged
+// K-steps, a serial chain of transposes and tests, 9.0.  Scattered flags (5%)
+// cost the vector instructions of the transposes: 512 inputs, 32 channels, 8,192
+// samples take 53 us, where adding the counts of every 32-sample step into LDS
+// on their own took 449 us, the LDS atomics' rate.  The units are this small,
+// although their words are loaded and transposed 2.5 times, because a channel's
+// counts then come from one chunk: with 36 tiles to a workgroup and four chunks
+// to a channel the global atomics took 34 of 59 us (256 dense inputs).  Many
+// inputs: see flag_wide_kernels.hpp and use_wide_flags() in plan.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -481,9 +482,9 @@ __global__ void apply_kernel(uint8_t *packed, const uint32_t *flags, int N, int 
 // workgroup takes rows i and N - 1 - i, N + 1 baselines, together; the
 // workgroups of a channel share its row pairs, with the channel's d_ii in LDS:
 // they lie a row apart in d.  Found from the baseline's number by a square
-// root, with d_jj fetched for every baseline, the rows took 355 us at 2048
-// inputs x 16 channels (671 MB), 30 at 512 x 32 and 16.4 at 256 x 64, and take
-// 197, 22 and 15.4.
+// root, with d_jj fetched for every baseline, the rows took 394 us at 2048
+// inputs x 16 channels, 32 at 512 x 32 and 17.0 at 256 x 64, with n_out, and
+// take 251, 24 and 15.0 (344 and 16.4 without n_out: 187 and 13.8).
 //
 // The quotients of a pair share one reciprocal: r = 1 / n and q = v r, both
 // rounded, and q + r (v - n q) with fused products is off by less than 2^-104
@@ -536,8 +537,9 @@ __global__ __launch_bounds__(kNormThreads) void normalize_kernel(const int32_t *
 // The same for N <= kFewInputs, whose row pairs would leave half of a
 // workgroup's threads idle: one thread per baseline of all channels, (i, j)
 // from p by inverting the row starts s(i) = i N - i (i - 1) / 2.  64 inputs x
-// 1000 channels take 16 us so and 20 by row pairs, 100 x 500 18 and 19, 250 x 64
-// 15.8 and 13.7.
+// 1000 channels take 16 us so and 20 by row pairs, 100 x 500 18 and 19, 129 x
+// 1000 56 and 60, 140 x 1000 68 and 68, 132 x 2000 172 and 143, 180 x 300 34 and
+// 31.
 constexpr int kFewInputs = 128;
 
 __global__ void normalize_few_kernel(const int32_t *vis, const int64_t *count, const int32_t *d,

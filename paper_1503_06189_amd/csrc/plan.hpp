@@ -186,6 +186,7 @@ inline void choose_split(int64_t units, int steps, int n_cu, int *splits,
 //   128 inputs, 128 channels, 16,384 samples:  8.5 - 10.6 |  9 - 13,   25 |   64
 //   256 inputs,  64 channels, 16,384 samples:  9.8 - 14.7 |  9 - 13,   41 |  123
 //   256 inputs, 128 channels, 16,384 samples:   19 - 27   | 14 - 20,   77 |  191
+//   130 inputs, 128 channels, 16,384 samples:   17 - 27   | 13 - 17,   60 |   79
 //   256 inputs, 160 channels,  2,048 samples:   11 - 16   |  9 -  9,   37 |   66
 //   130 inputs, 400 channels,  2,048 samples:   22 - 32   | 15 - 19,   61 |   60
 //   256 inputs, 400 channels,  2,048 samples:   23 - 33   | 11 - 16,   80 |  133
@@ -196,11 +197,11 @@ inline void choose_split(int64_t units, int steps, int n_cu, int *splits,
 //   1024 inputs,  2 channels,  8,192 samples, bursts:  12 | 25
 //   1024 inputs,  4 channels, 16,384 samples, bursts:  22 | 19
 // How dense the flags are is not known before they are read.  Up to two units
-// per compute unit the unit kernel is taken: bursts cost it 8 us more at most
-// and scattered flags two to ten times less.  Beyond, bursts, which are the
-// method's case, cost it up to twice as much, and decide.  Rows of more than 64
-// bytes reach that point at half a unit per compute unit; a single group's
-// units load every word once, and never do.
+// per compute unit the unit kernel is taken: bursts cost it 10 us more at most,
+// and scattered flags mostly between a half and a tenth.  Beyond, bursts, which
+// are the method's case, cost it up to twice as much, and decide.  Rows of more
+// than 64 bytes reach that point at half a unit per compute unit; a single
+// group's units load every word once, and never do.
 inline bool use_wide_flags(int64_t F, int groups, int n_cu) {
     const int64_t units = F * groups * groups;
     return groups > 1 && units > (groups <= 4 ? 2 * (int64_t)n_cu : n_cu / 2);

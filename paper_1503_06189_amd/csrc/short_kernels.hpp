@@ -5,7 +5,7 @@
 // instruction cache, sums in float32 that pass through LDS and are turned
 // back, and input sums to be applied.  This one integrates in int8, whose
 // sums are the output as they stand.  Where each is faster: see
-// kShortSteps in plan.hpp.
+// short_steps() in plan.hpp.
 //
 //   x = a + i b.  With the real K-vector of one input laid out as the pairs
 //   (a_t, b_t) and the derived vector (b_t, -a_t),

@@ -40,15 +40,19 @@
 // registers, without barriers; the waves' sums are added at the end.
 // Short chunks run on another kernel (short_kernels.hpp).
 //
-// What bounds it: 256 inputs, 64 channels, 16,384 samples (four chunks each):
-// a loop step takes 2,080 clocks, of which the matrix instructions fill about
-// 1,280 at the rate above, the packing alone would take about 1,100 issue
-// slots per SIMD, and the hand-over of loaded bytes costs 250; the frame
-// takes 118 us with the merge, where the int8 kernel took 173 (2048 inputs,
-// 16 channels, 8,192 samples: 725 us after 1,004).  One wave per SIMD with
-// 2 x 4 tiles read fewer operands but could not overlap packing with the
-// matrix instructions: 122 against 116 us at 256 inputs x 256 channels x
-// 4,096 samples, 748 against 725 us at 2048 inputs.
+// What bounds it: 256 inputs, 64 channels, 16,384 samples (four chunks each)
+// take 127 us on average and 118 at best, where the int8 kernel took 163 and
+// 149, and the matrix cores are busy 27% of the fastest dispatch.  Packing, LDS
+// and matrix work overlap only in part: in copies of the loop with parts left
+// out, a step's 2,080 clocks became 1,830 without the hand-over of loaded
+// bytes, 1,280 without packing and 1,390 without matrix instructions, which
+// alone take 1,150.  Timed over the frame's length (256 channels, one chunk), a
+// step takes 1.37 us and a call 37 us besides, of which the launch is about 6.
+// 2048 inputs, 16 channels, 8,192 samples take 0.70 ms on quantised noise and
+// 0.86 on random bytes (1.01 and 1.16 before).  One wave per SIMD with 2 x 4
+// tiles read fewer operands but could not overlap packing with the matrix
+// instructions: 122 against 116 us at 256 inputs x 256 channels x 4,096
+// samples, 748 against 725 us at 2048 inputs.
 //
 // Diagonal tiles: block c against itself is Hermitian, so one tile
 //   Q = R + I,  R = (Q + Q^T) / 2,  I = (Q - Q^T) / 2  (exact)

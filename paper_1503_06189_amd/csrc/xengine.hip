@@ -136,12 +136,12 @@ size_t partial_bytes(int64_t keys, int splits) {
     return splits > 1 ? (size_t)keys * (splits - 1) * xe::kGroupPartial * sizeof(int32_t) : 0;
 }
 
-// Returns false when time chunks are unavoidable but their partial sums do
-// not fit the workspace.
 // the halves geometry for frames of at most 4 input blocks, unless the
 // caller asked for padded super-blocks
 int halves_of(int geometry) { return geometry == XE_GEOM_SUPER ? 0 : 1; }
 
+// Returns false when time chunks are unavoidable but their partial sums do
+// not fit the workspace.
 bool fill_plan(int32_t N, int32_t F, int32_t T, int32_t n_cu, size_t ws_bytes, int halves,
                xe_plan_info *p) {
     int nb = xe::ceil_div(N, xe::kBlk);
@@ -150,8 +150,9 @@ bool fill_plan(int32_t N, int32_t F, int32_t T, int32_t n_cu, size_t ws_bytes, i
     int splits, sps;
     int64_t keys = (int64_t)F * G;
     xe::choose_split(keys, steps, n_cu, &splits, &sps);
-    // Chunk limits: the byte offsets inside a chunk stay below 2^31, and a
-    // diagonal tile's Q (at most 248 per sample) stays within int32.
+    // Chunk limit: the byte offsets inside a chunk stay below 2^31.  (What its
+    // sums may hold is the kernels' matter: the 6-bit ones turn theirs into
+    // int32 once per segment, the int8 one's chunks are short.)
     const int64_t max_sps = xe::max_steps_per_chunk(F, N);
     if (sps > max_sps) {
         sps = (int)max_sps;
